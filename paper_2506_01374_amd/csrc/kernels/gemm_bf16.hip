@@ -25,7 +25,9 @@
 //                NSTAGE buffers filled by direct-to-LDS buffer loads issued
 //                NSTAGE - 1 tiles ahead (range-checked: padded and missing
 //                rows load zeros), the next tile's first fragments read
-//                during the current tile's last k-step
+//                during the current tile's last k-step.  RING_FREE (set for
+//                variants that would spill otherwise) leaves the order of a
+//                k-step's loads, reads and MFMAs to the compiler
 //   VEC          bf16 elements per global load: 2, 4 or 8 (Vectorize)
 //   UNROLL       unroll factor of the K-tile loop (Unroll)
 //   LAYOUT       weights stored 0: [K][N], 1: [N][K] (Layout)
@@ -60,9 +62,9 @@
 //                never stored.
 //
 // LDS holds both operands as rows of TK bf16 (K contiguous).  16-byte
-// chunks are XOR-swizzled with the row so that the 16 lanes that share a
-// 128-bit LDS access cycle hit distinct banks, for fragment reads and for
-// row-major tile writes alike.
+// chunks are XOR-swizzled with the row (swz_x) so that the 16 lanes that
+// share a 128-bit LDS access cycle hit distinct banks, for fragment reads
+// and for row-major tile writes alike.
 //
 // The MFMA is issued with the weight fragment as its first operand and the
 // activation fragment as its second, so the accumulator holds C^T: each
@@ -113,6 +115,16 @@
 typedef unsigned short bf16_t;
 
 template <int V> struct IntC { static constexpr int value = V; };
+// seq<A, B>(f): f(IntC<A>), f(IntC<A + 1>), ... f(IntC<B - 1>), every index a
+// constant whatever the length (a loop left rolled would put the register
+// arrays it indexes into scratch memory)
+template <class T, T... I> struct ISeq {};
+template <int A, class F, int... I> __device__ __forceinline__ void seq_calls(F &f, ISeq<int, I...>) {
+    (f(IntC<A + I>{}), ...);
+}
+template <int A, int B, class F> __device__ __forceinline__ void seq(F &&f) {
+    if constexpr (B > A) seq_calls<A>(f, __make_integer_seq<ISeq, int, B - A>{});
+}
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -147,9 +159,24 @@ struct GemmBf16Args {
     const int *tile_start;  // MoE: first M tile of each expert [NEXP + 1]
 };
 
-__device__ __forceinline__ int swz(int row, int chunk) {
-    return row * TK + ((chunk ^ ((row / RPL) % CPR)) << 3);
+// XOR applied to a row's 16-byte chunk indices.  A ds_read_b128 is served in
+// groups of 16 lanes that are not consecutive: lanes 0-3, 12-15, 20-23 and
+// 24-27 go together, then 4-11, 16-19 and 28-31, and so on.  A fragment read
+// of MFMA shape 16 so mixes two chunks in one group (rows 0-3 and 12-15 of
+// chunk c with rows 4-11 of chunk c + 1), and its 16 lanes must land on
+// distinct 16-byte columns of the 256 bytes that the 64 banks span.  With 8
+// or 16 chunks a row (64- and 128-deep tiles) XOR by the row does that.
+// With 4 chunks (32-deep tiles, four rows to 256 bytes) XOR by the row block
+// g = row / 4 puts two of a group's four row blocks on one column; the
+// blocks take 0, 2, 3, 1 instead, which serves both MFMA shapes.
+__device__ __forceinline__ int swz_x(int row) {
+#ifndef RING_FREE      // (one register fewer where every one counts)
+    if (CPR == 4) return (0x78 >> (row / 2 % 8 & 6)) & 3;      // 0, 2, 3, 1 by row / 4 % 4
+#endif
+    return (row / RPL) % CPR;
 }
+
+__device__ __forceinline__ int swz(int row, int chunk) { return row * TK + ((chunk ^ swz_x(row)) << 3); }
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -217,7 +244,7 @@ void rc_gemm_bf16(GemmBf16Args args) {
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform: scalar registers
     const int wm = wave / WN, wn = wave % WN;
 
     // ---- workgroup -> tile --------------------------------------------
@@ -497,7 +524,7 @@ void rc_gemm_bf16(GemmBf16Args args) {
     // into 1 KiB of LDS at a wave-uniform base, lane i at byte 16 i.  The
     // swizzle is applied by choosing which global chunk each lane fetches:
     // LDS chunk c of the tile holds row c / CPR, logical chunk
-    // (c % CPR) ^ ((row / RPL) % CPR) of that row (the XOR is an involution).
+    // (c % CPR) ^ swz_x(row) of that row (the XOR is an involution).
     typedef __attribute__((address_space(3))) void *lds_vp;
     typedef __attribute__((address_space(1))) void *gbl_vp;
     constexpr int NWV = WM * WN;
@@ -509,7 +536,7 @@ void rc_gemm_bf16(GemmBf16Args args) {
 #pragma unroll
     for (int j = 0; j < A_WL; ++j) {
         const int c = (wave * A_WL + j) * 64 + lane;
-        const int row = c / CPR, lc = (c % CPR) ^ ((row / RPL) % CPR);
+        const int row = c / CPR, lc = (c % CPR) ^ swz_x(row);
 #if AMODE == 0
         // rows past GM read the tile's first row; their products are never stored
         a_src[j] = Ab + (size_t)(row_base + (RAGGED_M && row >= rows_valid ? 0 : row)) * GK + lc * 8;
@@ -526,7 +553,7 @@ void rc_gemm_bf16(GemmBf16Args args) {
 #pragma unroll
         for (int j = 0; j < B_WL; ++j) {
             const int c = (wave * B_WL + j) * 64 + lane;
-            const int row = c / CPR, lc = (c % CPR) ^ ((row / RPL) % CPR);
+            const int row = c / CPR, lc = (c % CPR) ^ swz_x(row);
             b_src[b][j] = (b == 0 ? B0 :
 #if NB == 2
                            B1
@@ -628,26 +655,23 @@ void rc_gemm_bf16(GemmBf16Args args) {
     rsB[1] = rsrc(B1, ((unsigned long long)GN * GK - KBASE) * 2);
 #endif
     // per-lane byte offsets of each wave-load at k0 = 0
-    unsigned a_off7[A_WL];
-    bool a_ok7[A_WL];
 #if AMODE == 2
     int a_cor7[A_WL];                                 // window corner (may lie in the padding), bytes
-    unsigned a_msk7[A_WL];
+    unsigned a_pad7[A_WL];                            // bit per filter tap: in the padding (or no such row)
+#else
+    unsigned a_off7[A_WL];                            // OOB for missing rows
 #endif
 #pragma unroll
     for (int j = 0; j < A_WL; ++j) {
         const int c = (wave * A_WL + j) * 64 + lane;
-        const int row = c / CPR, lc = (c % CPR) ^ ((row / RPL) % CPR);
+        const int row = c / CPR, lc = (c % CPR) ^ swz_x(row);
 #if AMODE == 0 || AMODE == 3
-        a_ok7[j] = row < rows_valid;
-        a_off7[j] = (unsigned)(((size_t)(row_base + row) * GK + lc * 8) * 2);
+        a_off7[j] = row < rows_valid ? (unsigned)(((size_t)(row_base + row) * GK + lc * 8) * 2) : OOB;
 #elif AMODE == 1
-        a_ok7[j] = row < rows_valid;
-        const int tok = args.perm[row_base + (a_ok7[j] ? row : 0)] / TOPK;
-        a_off7[j] = (unsigned)(((size_t)tok * GK + lc * 8) * 2);
+        const int tok = args.perm[row_base + (row < rows_valid ? row : 0)] / TOPK;
+        a_off7[j] = row < rows_valid ? (unsigned)(((size_t)tok * GK + lc * 8) * 2) : OOB;
 #else
         const int m = row_base + row;
-        a_ok7[j] = m < GM;
         const int n = m / (CV_P * CV_Q), p = (m / CV_Q) % CV_P, q = m % CV_Q;
         a_cor7[j] = 2 * (((n * CV_H + p - CV_PAD) * CV_W + (q - CV_PAD)) * CV_C + lc * 8);
         unsigned mask = 0;
@@ -656,45 +680,52 @@ void rc_gemm_bf16(GemmBf16Args args) {
             const int ih = p + tap / CV_S - CV_PAD, iw = q + tap % CV_S - CV_PAD;
             if (ih >= 0 && ih < CV_H && iw >= 0 && iw < CV_W) mask |= 1u << tap;
         }
-        a_msk7[j] = a_ok7[j] ? mask : 0u;
-        a_off7[j] = 0;
+        a_pad7[j] = m < GM ? ~mask : ~0u;
 #endif
     }
     unsigned b_off7[B_WL];
 #pragma unroll
     for (int j = 0; j < B_WL; ++j) {
         const int c = (wave * B_WL + j) * 64 + lane;
-        const int row = c / CPR, lc = (c % CPR) ^ ((row / RPL) % CPR);
+        const int row = c / CPR, lc = (c % CPR) ^ swz_x(row);
         b_off7[j] = (unsigned)(((size_t)(n0 + row) * GK + lc * 8) * 2);
     }
-    auto dma = [&](unsigned off, const i32x4 &rs, unsigned lds_addr) {
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-                     :: "v"(off), "s"(rs), "s"(lds_addr) : "memory", "m0");
+    // `koff` is wave-uniform and added to the lane's byte offset; the range
+    // check covers the sum, so an offset of OOB stays out of range
+    // (the readfirstlanes are free for values already in scalar registers;
+    // they make sure of it for the few variants where the compiler moves
+    // wave-uniform values to vector registers, which the asm cannot take)
+    auto dma = [&](unsigned off, const i32x4 &rs, unsigned koff, unsigned lds_addr) {
+        i32x4 rsu;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rsu[r] = rs[r];
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :: "v"(off), "s"(rsu), "s"(koff),
+                        "s"(lds_addr) : "memory", "m0");
     };
     const unsigned ring0 = (unsigned)(size_t)(lds_p)ring;
-    const int wv = __builtin_amdgcn_readfirstlane(wave);      // wave-uniform, in a scalar register
-    auto issue = [&](int kt, int st) {
+    // wave-load d (0 .. LPT - 1: the A tile's, then each weight tile's) of K
+    // tile kt into the stage whose LDS byte address is sb
+    auto issue_one = [&](int d, int kt, unsigned sb) {
         const int k0 = kt * TK;
-        const unsigned sb = ring0 + (unsigned)(st * STAGE_ELEMS * 2);
+        if (d < A_WL) {
 #if AMODE == 2
-        const int tap = k0 / CV_C;
-        const int tap_off = 2 * (((tap / CV_S) * CV_W + tap % CV_S) * CV_C + (k0 - tap * CV_C));
-#endif
-#pragma unroll
-        for (int j = 0; j < A_WL; ++j) {
-#if AMODE == 2
-            const unsigned off = ((a_msk7[j] >> tap) & 1u) ? (unsigned)(a_cor7[j] + tap_off) : OOB;
+            const int tap = k0 / CV_C;
+            const int tap_off = 2 * (((tap / CV_S) * CV_W + tap % CV_S) * CV_C + (k0 - tap * CV_C));
+            const unsigned off = (unsigned)(a_cor7[d] + tap_off) | (a_pad7[d] >> tap) << 31;
+            dma(off, rsA, 0u, sb + (unsigned)((wave * A_WL + d) * 1024));
 #else
-            const unsigned off = a_ok7[j] ? a_off7[j] + 2u * k0 : OOB;
+            dma(a_off7[d], rsA, 2u * k0, sb + (unsigned)((wave * A_WL + d) * 1024));
 #endif
-            dma(off, rsA, sb + (unsigned)((wv * A_WL + j) * 1024));
+        } else {
+            const int b = (d - A_WL) / B_WL, j = (d - A_WL) % B_WL;
+            dma(b_off7[j], rsB[b], 2u * k0,
+                sb + (unsigned)(TM * TK * 2 + b * TN * TK * 2 + (wave * B_WL + j) * 1024));
         }
+    };
+    auto issue = [&](int kt, unsigned sb) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int j = 0; j < B_WL; ++j)
-                dma(b_off7[j] + 2u * k0, rsB[b],
-                    sb + (unsigned)(TM * TK * 2 + b * TN * TK * 2 + (wv * B_WL + j) * 1024));
+        for (int d = 0; d < LPT; ++d) issue_one(d, kt, sb);
     };
     // s_waitcnt with only the vector-memory count constrained
 #define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | ((((n) >> 4) & 3) << 14) | (7 << 4) | (15 << 8))
@@ -732,11 +763,27 @@ void rc_gemm_bf16(GemmBf16Args args) {
             default: WAIT_VM(0); break;
         }
     };
-    auto stage_a = [&](int t) { return (const bf16_t *)(ring + (t % NSTAGE) * STAGE_ELEMS); };
     auto stage_b = [&](const bf16_t *la) { return (const bf16_t (*)[TN * TK])(la + TM * TK); };
-    // MFMAs of one k-step interleaved with the next k-step's fragment reads
-    constexpr int NMF = NB * FM * FN, NRD = FM + NB * FN;
-    auto kstep = [&](const Frags &cur, const bf16_t *ln, int ksn, Frags &nxt, auto part) {
+    constexpr int NMF = NB * FM * FN, NRD = FM + NB * FN;     // MFMAs and fragment reads of a k-step
+    // One k-step of a full tile: its MFMAs, with the next k-step's fragment
+    // reads (in the order those MFMAs use them, done by three quarters of the
+    // way) and this k-step's share of tile kt's loads spread between them.
+    // The matrix, LDS and vector-memory pipes each take about a third to a
+    // half of a tile's time, so a tile costs their maximum when they run side
+    // by side and their sum when a wave issues all of one kind before the
+    // next.  The scheduling barriers keep the order written here; the
+    // scheduler would otherwise gather the reads at the end of the k-step.
+    // (All loads first, then reads and MFMAs in the scheduler's order -> this
+    // order: 3 x 3 convolution 2 x 64 x 64 x 320 -> 320 in 64 x 160 x 64 tiles
+    // 25.4 -> 21.2 us; 1000 x 4096 x 4096 in 128 x 128 x 64 tiles 38.7 -> 33.7
+    // us; gated MLP 2048 x 4096 x 14336 639 -> 616 us, near the power limit;
+    // MoE 4096 tokens 551 -> 524 us; weight streams of 16 rows unchanged.)
+#ifdef RING_FREE
+    // The order left to the compiler, for the few register-bound variants
+    // that spill in the order above: a tile's loads first, then each
+    // k-step's fragment reads among its MFMAs.
+    auto kstep = [&](const Frags &cur, const bf16_t *ln, int ksn, Frags &nxt, auto, auto, int, unsigned,
+                     auto part) __attribute__((always_inline)) {
         load_frags(ln, stage_b(ln), ksn, nxt, part);
         mfmas(cur, part);
         if constexpr (!decltype(part)::value) {
@@ -748,41 +795,155 @@ void rc_gemm_bf16(GemmBf16Args args) {
             __builtin_amdgcn_sched_group_barrier(0x008, NMF, 0);
         }
     };
+#else
+    constexpr auto reads_before = [](int m) constexpr {
+        const int r = (m * NRD * 4 + 3 * NMF - 1) / (3 * NMF);
+        return r < NRD ? r : NRD;
+    };
+    auto kstep = [&](const Frags &cur, const bf16_t *ln, int ksn, Frags &nxt, auto ksc, auto loads, int kt, unsigned sb,
+                     auto) __attribute__((always_inline)) {
+        const bf16_t(*lb)[TN * TK] = stage_b(ln);
+        seq<0, NMF>([&](auto mc) __attribute__((always_inline)) {
+            constexpr int m = decltype(mc)::value;
+            seq<reads_before(m), reads_before(m + 1)>([&](auto rc) __attribute__((always_inline)) {
+                // a[0], b[0][..], a[1..], b[1][..]
+                constexpr int r = decltype(rc)::value;
+                if constexpr (r == 0 || (r > FN && r < FM + FN)) {
+                    constexpr int i = r == 0 ? 0 : r - FN;
+                    nxt.a[i] = *(const bf16x8 *)(ln + (wm * WTM + i * MF) * TK + foff[ksn]);
+                } else {
+                    constexpr int b = r > FN ? 1 : 0, j = b ? r - FM - FN : r - 1;
+                    nxt.b[b][j] = *(const bf16x8 *)(lb[b] + (wn * WTN + j * MF) * TK + foff[ksn]);
+                }
+            });
+            if constexpr (decltype(loads)::value) {
+                constexpr int s = decltype(ksc)::value * NMF + m;
+                seq<s * LPT / (KS * NMF), (s + 1) * LPT / (KS * NMF)>(
+                    [&](auto d) __attribute__((always_inline)) { issue_one(decltype(d)::value, kt, sb); });
+            }
+            constexpr int b = m / (FM * FN), i = m / FN % FM, j = m % FN;
+            acc[b][i][j] = mfma(cur.b[b][j], cur.a[i], acc[b][i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#if PART_TILES
+    // The same for a partial tile's wave, which reads and multiplies its
+    // fm_live live row blocks only: the next k-step's weight fragments and
+    // first row block are read ahead, the other row blocks two blocks ahead
+    // of their MFMAs (a second whole fragment set would not fit the registers
+    // next to the full tiles' loop).
+    auto a_frag = [&](const bf16_t *l, int i, int ks) {
+        return *(const bf16x8 *)(l + (wm * WTM + i * MF) * TK + foff[ks]);
+    };
+    auto b_frags = [&](const bf16_t *l, int ks, Frags &f) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) f.b[b][j] = *(const bf16x8 *)(stage_b(l)[b] + (wn * WTN + j * MF) * TK + foff[ks]);
+    };
+    auto kstep_part = [&](Frags &cur, const bf16_t *la, auto ksc, const bf16_t *ln, int ksn, Frags &nxt, auto loads, int kt,
+                          unsigned sb) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ksc)::value;
+        seq<0, FM>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            if constexpr (decltype(loads)::value) {
+                constexpr int s = ks * FM + i;
+                seq<s * LPT / (KS * FM), (s + 1) * LPT / (KS * FM)>(
+                    [&](auto d) __attribute__((always_inline)) { issue_one(decltype(d)::value, kt, sb); });
+            }
+            if (i < fm_live) {
+                if constexpr (i == 0) {
+                    if constexpr (FM > 1) cur.a[1] = a_frag(la, 1, ks);
+                    nxt.a[0] = a_frag(ln, 0, ksn);
+                    b_frags(ln, ksn, nxt);
+                }
+                if constexpr (i + 2 < FM) cur.a[i + 2] = a_frag(la, i + 2, ks);
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) acc[b][i][j] = mfma(cur.b[b][j], cur.a[i], acc[b][i][j]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#endif
+#endif
     Frags f7[2];
 #pragma unroll
     for (int u = 0; u < NSTAGE - 1; ++u)
-        if (u < KTILES) issue(u, u);
+        if (u < KTILES) issue(u, ring0 + (unsigned)(u * STAGE_ELEMS * 2));
     wait_tiles(min(NSTAGE - 2, KTILES - 1));
     __builtin_amdgcn_s_waitcnt(0xC07F);
     asm volatile("s_barrier" ::: "memory");
-    auto body7 = [&](int t, auto par, auto part) {
+    // Stages of tiles t, t + 1 and t - 1 (the one tile t + NSTAGE - 1 goes to)
+    int cur = 0, nx = NSTAGE > 1 ? 1 : 0, fill = NSTAGE - 1;
+    // `loads`: 1 - a tile of the steady part (tile t + NSTAGE - 1 exists),
+    // its loads spread over the MFMAs; 0 - one of the last tiles.
+    auto body7 = [&](int t, auto par, auto part, auto loads) __attribute__((always_inline)) {
         constexpr int P = decltype(par)::value;
-        if (t + 1 < KTILES) {
-            // tile t + 1 has landed; every wave is done with tile t - 1's stage
-            wait_tiles(min(KTILES - 1, t + NSTAGE - 2) - (t + 1));
-            __builtin_amdgcn_s_waitcnt(0xC07F);
+        constexpr bool STEADY = decltype(loads)::value;
+        [[maybe_unused]] constexpr bool PART = decltype(part)::value;
+        const unsigned sb = ring0 + (unsigned)(fill * (STAGE_ELEMS * 2));
+        // Tile t + 1 has landed; every wave is done with tile t - 1's stage:
+        // its last reads were consumed by MFMAs issued before this barrier
+        // (the scheduling barrier keeps them there), so only reads of tile
+        // t's own first k-step may still be in flight here.
+        __builtin_amdgcn_sched_barrier(0);
+        if (STEADY) {
+            WAIT_VM((NSTAGE - 3) * LPT);
             asm volatile("s_barrier" ::: "memory");
-            if (t + NSTAGE - 1 < KTILES) issue(t + NSTAGE - 1, (t + NSTAGE - 1) % NSTAGE);
+        } else if (t + 1 < KTILES) {
+            wait_tiles(min(KTILES - 1, t + NSTAGE - 2) - (t + 1));
+#ifdef RING_FREE
+            __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave's LDS reads are done
+#endif
+            asm volatile("s_barrier" ::: "memory");
+            if (t + NSTAGE - 1 < KTILES) issue(t + NSTAGE - 1, sb);
         }
-        const bf16_t *la = stage_a(t);
-        const bf16_t *ln = stage_a(t + 1);   // the last tile reads a stale stage; unused
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int ci = (P * KS + ks) & 1;          // a constant once unrolled
-            if (ks + 1 < KS) {
-                if (ci == 0) kstep(f7[0], la, ks + 1, f7[1], part);
-                else kstep(f7[1], la, ks + 1, f7[0], part);
-            } else {
-                if (ci == 0) kstep(f7[0], ln, 0, f7[1], part);
-                else kstep(f7[1], ln, 0, f7[0], part);
-            }
-        }
+        const bf16_t *la = ring + cur * STAGE_ELEMS;
+        const bf16_t *ln = ring + nx * STAGE_ELEMS;   // the last tile reads a stale stage; unused
+        seq<0, KS>([&](auto ksc) __attribute__((always_inline)) {
+            constexpr int ks = decltype(ksc)::value, ci = (P * KS + ks) & 1;
+            const bf16_t *lr = ks + 1 < KS ? la : ln;
+            constexpr int ksn = ks + 1 < KS ? ks + 1 : 0;
+#if PART_TILES && !defined(RING_FREE)
+            if constexpr (PART) kstep_part(f7[ci], la, ksc, lr, ksn, f7[1 - ci], loads, t + NSTAGE - 1, sb);
+            else
+#endif
+                kstep(f7[ci], lr, ksn, f7[1 - ci], ksc, loads, t + NSTAGE - 1, sb, part);
+        });
+        fill = cur;
+        cur = nx;
+        nx = nx + 1 == NSTAGE ? 0 : nx + 1;
     };
+    // tiles 0 .. STEADY_TILES - 1 (an even number) all have a tile to load
+#ifdef RING_FREE
+    constexpr int STEADY_TILES = 0;
+#else
+    constexpr int STEADY_TILES = KTILES >= NSTAGE ? ((KTILES - (NSTAGE - 1)) & ~1) : 0;
+#endif
     run_tiles([&](auto part) __attribute__((always_inline)) {
-        load_frags(stage_a(0), stage_b(stage_a(0)), 0, f7[0], part);
-        for (int t = 0; t < KTILES; t += 2) {
-            body7(t, IntC<0>{}, part);
-            if (t + 1 < KTILES) body7(t + 1, IntC<1>{}, part);
+#if PART_TILES && !defined(RING_FREE)
+        if constexpr (decltype(part)::value) {
+            if (fm_live > 0) {
+                f7[0].a[0] = a_frag(ring, 0, 0);
+                b_frags(ring, 0, f7[0]);
+            }
+        } else
+#endif
+            load_frags(ring, stage_b(ring), 0, f7[0], part);
+        int t = 0;
+#pragma nounroll
+        for (; t < STEADY_TILES; t += 2) {
+            body7(t, IntC<0>{}, part, IntC<1>{});
+            body7(t + 1, IntC<1>{}, part, IntC<1>{});
+        }
+#ifndef RING_FREE
+#pragma nounroll
+#endif
+        for (; t < KTILES; t += 2) {
+            body7(t, IntC<0>{}, part, IntC<0>{});
+            if (t + 1 < KTILES) body7(t + 1, IntC<1>{}, part, IntC<0>{});
         }
     });
 #undef WAIT_VM
@@ -814,7 +975,7 @@ void rc_gemm_bf16(GemmBf16Args args) {
     // wave-uniform and lives in scalar registers.
     constexpr int NX = CPR / 4;
     const int r_l = lane / CPR;
-    const int lc0 = (lane % CPR) ^ (r_l / RPL);
+    const int lc0 = (lane % CPR) ^ swz_x(r_l);
     unsigned voff[NX];
 #pragma unroll
     for (int x = 0; x < NX; ++x) voff[x] = (unsigned)(r_l * GK * 2 + ((lc0 ^ (4 * x)) << 4));

@@ -343,6 +343,25 @@ rc_status check_spill(const std::vector<char> &code, const char *entry) {
     return RC_OK;
 }
 
+std::string def(const char *name, long long v);
+
+// The code object of a kernel.  The ring GEMMs (stages 7) pin the order of
+// their loads, fragment reads and MFMAs, which a few variants at the register
+// limit cannot hold without spilling; those are compiled again with the order
+// left to the compiler.  `status` of check_spill on the returned code.
+rc_status build_kernel(const Source &s, std::vector<char> &code, std::string &key, rc_status &spill) {
+    rc_status r = compile(s, code, key);
+    if (r != RC_OK) return r;
+    spill = check_spill(code, s.entry);
+    if (spill != RC_ERR_ILLEGAL_SCHEDULE || s.defines.find("#define NSTAGE ") == std::string::npos) return RC_OK;
+    Source f = s;
+    f.defines += def("RING_FREE", 1);
+    r = compile(f, code, key);
+    if (r != RC_OK) return r;
+    spill = check_spill(code, s.entry);
+    return RC_OK;
+}
+
 std::string def(const char *name, long long v) {
     return std::string("#define ") + name + " " + std::to_string(v) + "\n";
 }
@@ -856,8 +875,9 @@ rc_status rc_precompile(const rc_op_desc *d, const rc_schedule *s, int32_t n, in
                 if (r != RC_OK) break;
                 std::vector<char> code;
                 std::string key;
-                r = compile(k.src, code, key);
-                if (r == RC_OK) r = check_spill(code, k.src.entry);
+                rc_status spill = RC_OK;
+                r = build_kernel(k.src, code, key, spill);
+                if (r == RC_OK) r = spill;
             }
             st[i] = r;
             if (r != RC_OK) ++nfail;
@@ -886,7 +906,8 @@ rc_status rc_describe(const rc_op_desc *d, const rc_schedule *s, rc_kernel_info 
     for (int32_t i = 0; i < *n; ++i) {
         std::vector<char> code;
         std::string key;
-        r = compile(p.kerns[i].src, code, key);
+        rc_status spill = RC_OK;
+        r = build_kernel(p.kerns[i].src, code, key, spill);
         if (r != RC_OK) return r;
         if (!buf || i >= cap) continue;
         rc_kernel_info k;
@@ -933,10 +954,10 @@ rc_status rc_plan_create(const rc_op_desc *d, const rc_schedule *s, rc_plan **ou
     for (auto &k : p->kerns) {
         std::vector<char> code;
         std::string key;
-        r = compile(k.src, code, key);
+        rc_status spill = RC_OK;
+        r = build_kernel(k.src, code, key, spill);
         if (r != RC_OK) return r;
-        r = check_spill(code, k.src.entry);
-        if (r != RC_OK) return r;
+        if (spill != RC_OK) return spill;
         hipModule_t mod;
         {
             std::lock_guard<std::mutex> g(g_mu);

@@ -504,6 +504,20 @@ GEMM_1X1_OP = (rc.RC_OP_CONV2D, (2, 16, 16, 256, 128, 1, 1, 0), rc.RC_FLAG_NO_AC
 CONV_FULL_ALT = _block("", 64, 64, 64, 4, 2, 16, 2, 8, 1, 1, 1) + ",fuse=1"
 
 
+# Ring GEMM (stages 7) around its depth: 90 rows (a partial last tile) of a
+# 1 x 1 convolution without activation whose K is 1 tile, 2 tiles, and from
+# one tile below the ring's depth (10 stages for each of these tiles) to
+# three above it; one and two k-steps a tile, both MFMA shapes.
+RING_EDGE_TILES = (1, 2, 9, 10, 11, 12, 13)
+RING_EDGE_BLOCKS = [(64, 64, 32, 2, 2, 16, 7, 8, 1, 1, 1, 2), (64, 64, 32, 2, 2, 32, 7, 8, 1, 1, 0, 2),
+                    (64, 64, 64, 2, 2, 16, 7, 8, 1, 1, 2, 1)]
+
+
+def ring_edge_jobs():
+    return [(rc.Op(rc.RC_OP_CONV2D, (1, 10, 9, b[2] * n, 64, 1, 1, 0), rc.RC_FLAG_NO_ACT), _block("", *b) + ",fuse=1")
+            for b in RING_EDGE_BLOCKS for n in RING_EDGE_TILES]
+
+
 # Schedules the search can emit: random legal transformation sequences of
 # length 12 from P0 (the rollouts of Sec. 3.2), seeded, at the small shapes.
 WALK_KEYS = ("gemm", "attn_causal", "mlp", "moe", "conv")
@@ -553,6 +567,8 @@ def all_compile_jobs():
     op = rc.Op(rc.RC_OP_CONV2D, W.workload_op("conv3x3_n2_64x64_c320_k320").dims, rc.RC_FLAG_NO_ACT)
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
+    for op, text in ring_edge_jobs():
+        jobs.append((op, [op.from_string(text)]))
     for kind, big, small, flags, text in NOALLOC_PAIRS:
         for dims in (big, small):
             op = rc.Op(kind, dims, flags)

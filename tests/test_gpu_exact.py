@@ -200,6 +200,22 @@ def test_bf16_gemm_integer_inputs_bitwise(sched_text):
     assert np.all(W.output_to_f64(op, out) == C)
 
 
+@pytest.mark.parametrize("job", range(len(cases.RING_EDGE_BLOCKS) * len(cases.RING_EDGE_TILES)))
+def test_ring_gemm_depth_edges_integer_inputs_bitwise(job):
+    # |x|, |w|, |bias| <= 8 and at most 13 x 64 products: integers below
+    # 2^24, so the bf16 rounding of the exact sum is the only right answer.
+    op, text = cases.ring_edge_jobs()[job]
+    N, H, Wd, C, K = op.dims[:5]
+    sched = op.from_string(text)
+    assert sched.validate() == ""
+    host = _int_conv_inputs(N, H, Wd, C, K, 1, 1, seed=17)
+    _, _, out, _ = launch(op, sched, host)
+    exact = (oracle.bf16_to_f64(host["x"]).reshape(-1, C) @ oracle.bf16_to_f64(host["w"]).reshape(K, C).T
+             + host["bias"].astype(np.float64)[None, :])
+    assert np.array_equal(W.output_to_f64(op, out).reshape(-1, K),
+                          oracle.bf16_to_f64(oracle.bf16_from_f64(exact)).reshape(-1, K))
+
+
 @pytest.mark.parametrize("sched_text", ["tuned", "default", cases.CONV_FULL_ALT])
 def test_conv_full_size_ones_padding_counts(sched_text):
     # Ones input, ones filters, zero bias, no activation: interior outputs
