@@ -5,8 +5,11 @@
 //   TM TN TK     workgroup tile (TileSize)
 //   WM WN        waves per workgroup along M and N (Parallel)
 //   VEC          fp32 elements per global load (Vectorize)
-//   STAGES       1: load-store-compute; 2: LDS double buffer with register
-//                prefetch of the next K tile (ComputeLocation); 3: streaming
+//   STAGES       1: load-store-compute; 2: the next K tiles on their way while
+//                one is computed (ComputeLocation): a ring of LDS buffers
+//                filled by direct-to-LDS loads where the tile allows it
+//                (RING below), else an LDS double buffer with register
+//                prefetch of the next K tile; 3: streaming
 //                for decode-shaped operators (M <= 16 rows, one MFMA row
 //                block): no LDS staging, each wave streams its own slice of
 //                the K range straight from memory into MFMA operands with
@@ -35,6 +38,12 @@
 #define FN (WTN / 16)
 #define KTILES ((GK + TK - 1) / TK)
 #define RAGGED ((GM % TM) != 0 || (GN % TN) != 0 || (GK % TK) != 0)
+// Stages 2 runs as a ring of NST LDS buffers when the loads are 16-byte
+// vectors, a K tile is whole 16-row MFMA blocks, its 1 KiB wave-loads split
+// evenly over the waves and 32-bit buffer offsets reach both operands.
+#define WLOADS ((TM * TK + TN * TK) / 256)
+#define RING (STAGES == 2 && VEC == 4 && TK >= 16 && WLOADS % (WM * WN) == 0 &&                       \
+              4ull * GM * GK < 0x80000000ull && 4ull * GK * GN < 0x80000000ull)
 #define A_LOADS ((TM * TK) / (VEC * NT))
 #define B_LOADS ((TK * TN) / (VEC * NT))
 
@@ -182,6 +191,239 @@ extern "C" __global__ __launch_bounds__(256) void rc_gemm_f32_splitk_reduce(Gemm
     if (g == 0 && ok) *(f32x4 *)(args.C + 4 * i) = ((part[0][t] + part[1][t]) + part[2][t]) + part[3][t];
 }
 #endif
+
+#elif RING
+// Ring variant.  What bounds the double-buffered loop at ordinary sizes is
+// the memory latency: a K tile of a 64 x 32 tile is 512 matrix cycles a
+// wave, and one tile ahead the next one's loads had about three waves' worth
+// of that to arrive in.  Here three tiles are on their way (NST - 1), without
+// registers: the loads go straight to LDS, 64 lanes x 16 bytes to 1 KiB.
+//
+// The loads go through buffer resources whose range check returns zeros:
+// vectors past M, N or K get offset OOB (VEC divides the row lengths, so a
+// vector is wholly inside or outside).  LDS holds A as rows of TK floats and
+// B as rows of TN (LAYOUT 0) or, like A, of TK floats (LAYOUT 1).  A lane
+// feeds four k-steps from one 16-byte read of A: k-step e of the 16-row
+// block kb contracts rows kb + 4 q + e (q = lane / 16, the MFMA's k slot).
+// The 16-byte chunks of a row are XOR-swizzled (by the choice of the global
+// chunk a lane loads) so that the lanes of one LDS access hit distinct banks:
+//   rows of TK floats: a ds_read_b128 is served 16 lanes at a time, lanes
+//     0-3, 12-15, 20-23 and 24-27 together, so a group mixes rows 0-3 and
+//     12-15 of one chunk with rows 4-11 of the next; XOR by row / 2 for 8
+//     chunks a row, by 0, 2, 3, 1 for the row blocks of 4 with 4 chunks
+//   rows of TN floats: the four rows 4 q + e that a ds_read_b32 reads 16
+//     columns of sit next to each other (row k of a 16-row block at position
+//     4 (k % 4) + k / 4) and take the four 64-byte spans of the banks in turn
+// A tile's loads, the next block's fragment reads and the MFMAs are spread
+// among each other in a pinned order (UNROLL has no effect here: the loop is
+// always unrolled by two tiles).  1000 x 1364 x 900 in 64 x 32 x 32 tiles:
+// 34.9 us double-buffered, 29.7 us with the ring and each tile's loads, reads
+// and MFMAs in turn, 27.6 us (89 TFLOP/s) interleaved; the 688 tiles are 2.7 a
+// CU, and the three of the fuller ones take 18.6 us of matrix time.
+#define NST 4
+#define NW (WM * WN)
+#define LPW (WLOADS / NW)                        // wave-loads per wave and K tile
+#define A_WL (TM * TK / 256)                     // wave-loads of the A tile (the rest are B's)
+#define STAGE_FLOATS ((TM + TN) * TK)
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+template <int V> struct IntC { static constexpr int value = V; };
+// seq<A, B>(f): f(IntC<A>), ... f(IntC<B - 1>), every index a constant
+template <class T, T... I> struct ISeq {};
+template <int A, class F, int... I> __device__ __forceinline__ void seq_calls(F &f, ISeq<int, I...>) {
+    (f(IntC<A + I>{}), ...);
+}
+template <int A, int B, class F> __device__ __forceinline__ void seq(F &&f) {
+    if constexpr (B > A) seq_calls<A>(f, __make_integer_seq<ISeq, int, B - A>{});
+}
+
+__device__ __forceinline__ int kswz(int row) {   // XOR of a TK-float row's chunk indices
+    return TK == 32 ? (row / 2) % 8 : (0x78 >> (row / 2 % 8 & 6)) & 3;
+}
+// position of row k of the B tile (LAYOUT 0) in LDS, and back
+__device__ __forceinline__ int brow(int k) { return (k & ~15) + 4 * (k & 3) + ((k >> 2) & 3); }
+// XOR of the chunk indices of the TN-float row at position p
+__device__ __forceinline__ int nswz(int p) { return TN == 64 ? 4 * (p & 3) : TN == 32 ? 4 * ((p >> 1) & 1) : 0; }
+
+extern "C" __global__ __launch_bounds__(NT) void rc_gemm_f32(GemmF32Args args) {
+    __shared__ __attribute__((aligned(16))) float ring[NST * STAGE_FLOATS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int q = lane >> 4, c = lane & 15;
+    // Workgroups reach the 8 XCDs round-robin: each XCD takes a contiguous
+    // range of the tiles (n fastest), whose operands its L2 then shares.
+    constexpr int NTN = (GN + TN - 1) / TN, NTILES = NTN * ((GM + TM - 1) / TM);
+    const int bid = blockIdx.y * NTN + blockIdx.x, xcd = bid & 7;
+    const int item = xcd * (NTILES / 8) + min(xcd, NTILES % 8) + (bid >> 3);
+    const int m0 = item / NTN * TM, n0 = item % NTN * TN;
+
+    constexpr unsigned OOB = 0x80000000u;        // past both operands: loads zeros
+    auto rsrc = [](const void *base, unsigned bytes) {
+        const unsigned long long a = (unsigned long long)base;
+        i32x4 r;
+        r[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)a);
+        r[1] = __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xFFFFu));   // stride 0
+        r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+        r[3] = 0x00020000;                                                             // raw dword access
+        return r;
+    };
+    const i32x4 rsA = rsrc(args.A, 4u * GM * GK), rsB = rsrc(args.B, 4u * GK * GN);
+    // this wave's loads: wave-load i * NW + wave of the tile (A's, then B's);
+    // the lane's byte offset at K tile 0 and its row of K within the tile
+    unsigned off[LPW];
+    int krow[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int w = i * NW + wave;
+        if (w < A_WL) {
+            const int ch = w * 64 + lane, row = ch / (TK / 4), col = 4 * ((ch % (TK / 4)) ^ kswz(row));
+            krow[i] = col;
+            off[i] = m0 + row < GM ? 4u * ((unsigned)(m0 + row) * GK + col) : OOB;
+        } else {
+            const int ch = (w - A_WL) * 64 + lane;
+#if LAYOUT == 0
+            const int p = ch / (TN / 4), col = 4 * ((ch % (TN / 4)) ^ nswz(p)), k = brow(p);
+            krow[i] = k;
+            off[i] = n0 + col < GN ? 4u * ((unsigned)k * GN + n0 + col) : OOB;
+#else
+            const int row = ch / (TK / 4), col = 4 * ((ch % (TK / 4)) ^ kswz(row));
+            krow[i] = col;
+            off[i] = n0 + row < GN ? 4u * ((unsigned)(n0 + row) * GK + col) : OOB;
+#endif
+        }
+    }
+    typedef __attribute__((address_space(3))) float *lds_p;
+    const unsigned ring0 = (unsigned)(size_t)(lds_p)ring;
+    auto issue_one = [&](auto ic, int t, int st) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        const int w = i * NW + wave;
+        const bool is_a = w < A_WL;
+        i32x4 rs;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rs[r] = is_a ? rsA[r] : rsB[r];
+        const unsigned step = is_a || LAYOUT == 1 ? 4u * TK : 4u * TK * GN;
+        // past the end of K: offset with its top bit set, out of range
+        const unsigned o = off[i] | (GK % TK != 0 ? (unsigned)(GK - t * TK - 1 - krow[i]) & OOB : 0u);
+        const unsigned koff = t * step, lds = ring0 + 4u * (st * STAGE_FLOATS) + w * 1024u;
+        // inline assembly: invisible to the compiler's wait-count
+        // bookkeeping, ordered by the waits below
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                     :: "v"(o), "s"(rs), "s"(koff), "s"(lds) : "memory", "m0");
+    };
+    auto issue = [&](int t, int st) __attribute__((always_inline)) {
+        seq<0, LPW>([&](auto i) __attribute__((always_inline)) { issue_one(i, t, st); });
+    };
+#define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | ((((n) >> 4) & 3) << 14) | (7 << 4) | (15 << 8))
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // fragments of one 16-row block of K: element e feeds k-step e
+    struct Frags {
+        f32x4 a[FM], b[FN];
+    };
+    constexpr int NKB = TK / 16, NMF = 4 * FM * FN, NBR = LAYOUT == 0 ? 4 * FN : FN, NRD = FM + NBR;
+    auto read_one = [&](auto rc, const float *As, int kb, Frags &f) __attribute__((always_inline)) {
+        constexpr int r = decltype(rc)::value;
+        if constexpr (r < FM) {
+            f.a[r] = *(const f32x4 *)(As + (wm * WTM + r * 16 + c) * TK + 4 * ((kb / 4 + q) ^ kswz(c)));
+        } else {
+            const float *Bs = As + TM * TK;
+#if LAYOUT == 0
+            constexpr int e = (r - FM) / FN, j = (r - FM) % FN, p = 4 * e;     // position of row kb + 4 q + e: kb + p + q
+            f.b[j][e] = Bs[(kb + p + q) * TN + ((wn * WTN + j * 16 + c) ^ (4 * nswz(p + q)))];
+#else
+            constexpr int j = r - FM;
+            f.b[j] = *(const f32x4 *)(Bs + (wn * WTN + j * 16 + c) * TK + 4 * ((kb / 4 + q) ^ kswz(c)));
+#endif
+        }
+    };
+    // One block: its MFMAs, with the next block's fragment reads and, in the
+    // steady part, a share of tile t + NST - 1's loads spread between them
+    // (the order is pinned: the pipes run side by side).
+    auto block = [&](const Frags &f, auto kbc, const float *An, int kbn, Frags &nxt, auto steady, int t, int st)
+                     __attribute__((always_inline)) {
+        seq<0, NMF>([&](auto mc) __attribute__((always_inline)) {
+            constexpr int m = decltype(mc)::value, e = m / (FM * FN), i = m / FN % FM, j = m % FN;
+            seq<m * NRD / NMF, (m + 1) * NRD / NMF>([&](auto r) __attribute__((always_inline)) { read_one(r, An, kbn, nxt); });
+            if constexpr (decltype(steady)::value) {
+                constexpr int s = decltype(kbc)::value * NMF + m;
+                seq<s * LPW / (NKB * NMF), (s + 1) * LPW / (NKB * NMF)>(
+                    [&](auto d) __attribute__((always_inline)) { issue_one(d, t + NST - 1, st); });
+            }
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[i][e], f.b[j][e], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+#pragma unroll
+    for (int u = 0; u < NST - 1; ++u)
+        if (u < KTILES) issue(u, u);
+    if (KTILES > 2) {
+        WAIT_VM(2 * LPW);
+    } else if (KTILES > 1) {
+        WAIT_VM(LPW);
+    } else {
+        WAIT_VM(0);
+    }
+    asm volatile("s_barrier" ::: "memory");
+    Frags f[2];
+    seq<0, NRD>([&](auto r) __attribute__((always_inline)) { read_one(r, ring, 0, f[0]); });
+    int cur = 0;
+    auto tile = [&](int t, auto par, auto steady) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value;
+        const int nx = (cur + 1) % NST, st = (cur + NST - 1) % NST;
+        // Tile t + 1 has landed (of the steady part's tiles t + 2 is in
+        // flight), and every wave is done with tile t - 1, whose buffer tile
+        // t + NST - 1 takes: its reads were consumed by MFMAs issued before.
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(steady)::value) {
+            WAIT_VM(LPW);
+            asm volatile("s_barrier" ::: "memory");
+        } else if (t + 1 < KTILES) {
+            if (t + 2 < KTILES) {
+                WAIT_VM(LPW);
+            } else {
+                WAIT_VM(0);
+            }
+            asm volatile("s_barrier" ::: "memory");
+            if (t + NST - 1 < KTILES) issue(t + NST - 1, st);
+        }
+        const float *As = ring + cur * STAGE_FLOATS, *An = ring + nx * STAGE_FLOATS;  // the last tile reads a stale stage; unused
+        seq<0, NKB>([&](auto kbc) __attribute__((always_inline)) {
+            constexpr int kb = decltype(kbc)::value, ci = (P * NKB + kb) & 1;
+            block(f[ci], kbc, kb + 1 < NKB ? As : An, kb + 1 < NKB ? 16 * (kb + 1) : 0, f[1 - ci], steady, t, st);
+        });
+        cur = nx;
+    };
+    constexpr int STEADY_TILES = KTILES >= NST ? ((KTILES - (NST - 1)) & ~1) : 0;
+    int t = 0;
+#pragma nounroll
+    for (; t < STEADY_TILES; t += 2) {
+        tile(t, IntC<0>{}, IntC<1>{});
+        tile(t + 1, IntC<1>{}, IntC<1>{});
+    }
+#pragma nounroll
+    for (; t < KTILES; t += 2) {
+        tile(t, IntC<0>{}, IntC<0>{});
+        if (t + 1 < KTILES) tile(t + 1, IntC<1>{}, IntC<0>{});
+    }
+#undef WAIT_VM
+
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = m0 + wm * WTM + i * 16 + 4 * q + r, n = n0 + wn * WTN + j * 16 + c;
+                if (!RAGGED || (m < GM && n < GN)) args.C[(size_t)m * GN + n] = acc[i][j][r];
+            }
+}
 
 #else
 extern "C" __global__ __launch_bounds__(NT) void rc_gemm_f32(GemmF32Args args) {

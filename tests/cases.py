@@ -518,6 +518,25 @@ def ring_edge_jobs():
             for b in RING_EDGE_BLOCKS for n in RING_EDGE_TILES]
 
 
+# fp32 ring (stages 2, 16-byte vectors, whole 16-row blocks of K): K of one
+# tile and less, around the ring's four buffers, and a last tile of one
+# vector; rows and columns past the edges; both layouts of B; every tile_n
+# (its swizzle differs) and both tile_k.
+GEMM_RING_K = (20, 32, 64, 96, 100, 128, 132, 260)
+GEMM_RING_TILES = [(64, 32, 32, 2, 2, 0), (16, 32, 32, 1, 2, 0), (32, 64, 16, 1, 2, 0), (16, 16, 16, 1, 1, 0),
+                   (64, 64, 32, 2, 2, 1), (32, 16, 16, 1, 1, 1)]
+
+
+def gemm_ring_jobs():
+    jobs = []
+    for tm, tn, tk, wm, wn, lay in GEMM_RING_TILES:
+        text = (f"tile_m={tm},tile_n={tn},tile_k={tk},waves_m={wm},waves_n={wn},vec=4,stages=2,unroll=1,"
+                f"layout={lay}")
+        for k in GEMM_RING_K:
+            jobs.append((rc.Op(rc.RC_OP_GEMM_F32, (83, 92, k)), text))
+    return jobs
+
+
 # Schedules the search can emit: random legal transformation sequences of
 # length 12 from P0 (the rollouts of Sec. 3.2), seeded, at the small shapes.
 WALK_KEYS = ("gemm", "attn_causal", "mlp", "moe", "conv")
@@ -567,7 +586,7 @@ def all_compile_jobs():
     op = rc.Op(rc.RC_OP_CONV2D, W.workload_op("conv3x3_n2_64x64_c320_k320").dims, rc.RC_FLAG_NO_ACT)
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
-    for op, text in ring_edge_jobs():
+    for op, text in ring_edge_jobs() + gemm_ring_jobs():
         jobs.append((op, [op.from_string(text)]))
     for kind, big, small, flags, text in NOALLOC_PAIRS:
         for dims in (big, small):

@@ -216,6 +216,18 @@ def test_ring_gemm_depth_edges_integer_inputs_bitwise(job):
                           oracle.bf16_to_f64(oracle.bf16_from_f64(exact)).reshape(-1, K))
 
 
+@pytest.mark.parametrize("job", range(len(cases.GEMM_RING_TILES) * len(cases.GEMM_RING_K)))
+def test_fp32_ring_edges_integer_inputs_bitwise(job):
+    # Integers in [-4, 4]: every partial sum is exact in fp32 in any order.
+    op, text = cases.gemm_ring_jobs()[job]
+    M, N, K = op.dims
+    sched = op.from_string(text)
+    assert sched.validate() == ""
+    host = {"A": gen.int_valued_f32(19, 1, (M, K), 4), "B": gen.int_valued_f32(19, 2, (K, N), 4)}
+    _, _, out, _ = launch(op, sched, host)
+    assert np.array_equal(W.output_to_f64(op, out), host["A"].astype(np.float64) @ host["B"].astype(np.float64))
+
+
 @pytest.mark.parametrize("sched_text", ["tuned", "default", cases.CONV_FULL_ALT])
 def test_conv_full_size_ones_padding_counts(sched_text):
     # Ones input, ones filters, zero bias, no activation: interior outputs
