@@ -63,6 +63,11 @@
 // direct-to-LDS paths: ring slots per operand (two per split with several
 // splits)
 #define RING (STAGES == 5 ? 4 * SPLITS : SPLITS > 1 ? 2 * SPLITS : 3)
+// Two key splits of four waves each whose ring (4 RING BN AD bytes) leaves room
+// for one workgroup per CU take turns on the matrix cores (measured below)
+#ifndef PINGPONG
+#define PINGPONG (STAGES == 4 && SPLITS == 2 && NW == 4 && 4 * RING * BN * AD > 81920)
+#endif
 #define KB (BN / MF)
 #define DB (AD / MF)
 #define NQT ((AS + BM - 1) / BM)
@@ -96,6 +101,14 @@
 
 typedef unsigned short bf16_t;
 template <int V> struct IntC { static constexpr int value = V; };
+// seq<A, B>(f): f(IntC<A>), ... f(IntC<B - 1>), every index a constant
+template <class T, T... I> struct ISeq {};
+template <int A, class F, int... I> __device__ __forceinline__ void seq_calls(F &f, ISeq<int, I...>) {
+    (f(IntC<A + I>{}), ...);
+}
+template <int A, int B, class F> __device__ __forceinline__ void seq(F &&f) {
+    if constexpr (B > A) seq_calls<A>(f, __make_integer_seq<ISeq, int, B - A>{});
+}
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -354,29 +367,26 @@ void rc_attention(AttnArgs args) {
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :: "v"(off), "s"(gbase), "s"(lds_addr) : "memory", "m0");
     };
-    // tile kt into ring buffer b
-    auto gload_lds = [&](int kt, int b) {
-        const bf16_t *Kg = args.K + base + (size_t)(kt0 + kt) * BN * AD;
-        const bf16_t *Vg = args.V + base + (size_t)(kt0 + kt) * BN * AD;
+    // this wave's loads j0 .. j1 - 1 of K (or V) of tile kt to LDS address lds
+    auto gload_op = [&](const bf16_t *src, const unsigned (&off)[WL], int kt, unsigned lds, int j0, int j1)
+                        __attribute__((always_inline)) {
+        const bf16_t *g = src + base + (size_t)(kt0 + kt) * BN * AD;
         const int kvalid = AS - (kt0 + kt) * BN;     // wave-uniform
         if (RAGGED_S && kvalid < BN) {
             // last, partial tile: rows past the sequence fetch its last row
 #pragma unroll
-            for (int j = 0; j < WL; ++j) {
+            for (int j = j0; j < j1; ++j) {
                 const unsigned back = 2u * AD * (unsigned)max(kv_row[RAGGED_S ? j : 0] - (kvalid - 1), 0);
-                dma(Kg, k_src[j] - back, KA(b) + j * 1024u);
-            }
-#pragma unroll
-            for (int j = 0; j < WL; ++j) {
-                const unsigned back = 2u * AD * (unsigned)max(kv_row[RAGGED_S ? j : 0] - (kvalid - 1), 0);
-                dma(Vg, v_src[j] - back, VA(b) + j * 1024u);
+                dma(g, off[j] - back, lds + j * 1024u);
             }
             return;
         }
 #pragma unroll
-        for (int j = 0; j < WL; ++j) dma(Kg, k_src[j], KA(b) + j * 1024u);
-#pragma unroll
-        for (int j = 0; j < WL; ++j) dma(Vg, v_src[j], VA(b) + j * 1024u);
+        for (int j = j0; j < j1; ++j) dma(g, off[j], lds + j * 1024u);
+    };
+    auto gload_lds = [&](int kt, int b) {
+        gload_op(args.K, k_src, kt, KA(b), 0, WL);
+        gload_op(args.V, v_src, kt, VA(b), 0, WL);
     };
 #if STAGES == 5
     // split sp's first three tiles (sp, sp + SPLITS, sp + 2 SPLITS) are in
@@ -392,6 +402,7 @@ void rc_attention(AttnArgs args) {
 #else
     // split sp's first tile (tile sp) is in flight while Q is read
     if (sp < n_kt) gload_lds(sp, sp);
+    if (PINGPONG && SPLITS + sp < n_kt) gload_op(args.K, k_src, SPLITS + sp, KA(SPLITS + sp), 0, WL);
 #endif
 #endif
     bf16x8 qf[QB][AD / KSTEP];
@@ -413,10 +424,10 @@ void rc_attention(AttnArgs args) {
 #endif
 
     accT o[QB][DB];
-    float m[QB], l[QB];
+    float m[QB], l[QB], vlim[QB];      // vlim: the score past which m moves
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        m[qb] = -__builtin_inff();
+        m[qb] = vlim[qb] = -__builtin_inff();
         l[qb] = 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -424,6 +435,32 @@ void rc_attention(AttnArgs args) {
             for (int r = 0; r < ACCN; ++r) o[qb][db][r] = 0.f;
     }
 
+    // largest score of this lane's keys
+    auto lane_max = [&](const accT (&s)[KB]) __attribute__((always_inline)) {
+        float v = -__builtin_inff();
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int r = 0; r < ACCN; ++r) v = fmaxf(v, s[kb][r]);
+        return v;
+    };
+    // Moves the running maximum (and rescales O and l) if some lane's largest
+    // score lies past the limit.  A query's maximum is past it exactly when
+    // one of its lanes' is, so the reduction across the lanes of a query,
+    // a chain of swaps and waits, is left to the tiles that do move it.
+    auto rescale = [&](int qb, float v) __attribute__((always_inline)) {
+        if (__builtin_amdgcn_ballot_w64(v > vlim[qb]) != 0) {
+            const float mnew = fmaxf(m[qb], group_max(v) * SCALE_LOG2);
+            const float alpha = __builtin_amdgcn_exp2f(m[qb] - mnew);
+            l[qb] *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < ACCN; ++r) o[qb][db][r] *= alpha;
+            m[qb] = mnew;
+            vlim[qb] = (mnew + RESCALE_LOG2) * (1.0f / SCALE_LOG2);
+        }
+    };
 
     vecT rk[K_LOADS];
     u32x4 rv[V_BLKS][4];
@@ -598,7 +635,6 @@ void rc_attention(AttnArgs args) {
 #endif
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float mx = -__builtin_inff();
 #if CAUSAL
             if (diag) {
                 const int q = q0w + qb * MF + lane % MF;
@@ -617,21 +653,7 @@ void rc_attention(AttnArgs args) {
                         if ((kt0 + kt) * BN + kb * MF + key_of(r, lane) >= AS) sc[qb][kb][r] = -__builtin_inff();
             }
 #endif
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int r = 0; r < ACCN; ++r) mx = fmaxf(mx, sc[qb][kb][r]);
-            mx = group_max(mx) * SCALE_LOG2;
-            if (__builtin_amdgcn_ballot_w64(mx > m[qb] + RESCALE_LOG2) != 0) {
-                const float mnew = fmaxf(m[qb], mx);
-                const float alpha = __builtin_amdgcn_exp2f(m[qb] - mnew);
-                l[qb] *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int r = 0; r < ACCN; ++r) o[qb][db][r] *= alpha;
-                m[qb] = mnew;
-            }
+            rescale(qb, lane_max(sc[qb]));
             const float mnew = m[qb];
             float ps = 0.f;
 #pragma unroll
@@ -705,7 +727,209 @@ void rc_attention(AttnArgs args) {
     // split sp visits key tiles sp, sp + SPLITS, ...; every wave runs the same
     // number of iterations so the workgroup barriers line up
     const int n_it = (n_kt + SPLITS - 1) / SPLITS;
-#if STAGES == 4 && SPLITS > 1
+#if STAGES == 5 || PINGPONG
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4i16 *lds_v4p;
+    auto needs_mask = [&](int kt) {
+#if CAUSAL
+        return (kt0 + kt) * BN + BN - 1 > q0w;
+#else
+        return RAGGED_S && (kt0 + kt) * BN + BN > AS;
+#endif
+    };
+    auto mask = [&](int kt, accT (&sc)[QB][KB]) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+#if CAUSAL
+            const int q = q0w + qb * MF + lane % MF;
+#else
+            const int q = AS - 1;      // keys past the sequence
+#endif
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int r = 0; r < ACCN; ++r)
+                    if ((kt0 + kt) * BN + kb * MF + key_of(r, lane) > q) sc[qb][kb][r] = -__builtin_inff();
+        }
+    };
+    // largest score of each query block's tile, per lane
+    auto tile_max = [&](const accT (&sc)[QB][KB], float (&mx)[QB]) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) mx[qb] = lane_max(sc[qb]);
+    };
+    auto rescale_all = [&](const float (&mx)[QB]) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) rescale(qb, mx[qb]);
+    };
+    // probabilities of a tile, packed into the P^T fragments of the P V product
+    auto probs = [&](accT (&sc)[QB][KB], bf16x8 (&pf)[BN / KSTEP][QB]) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            float ps = l[qb];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int r = 0; r < ACCN; ++r) {
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[qb][kb][r], SCALE_LOG2, -m[qb]));
+                    sc[qb][kb][r] = p;
+                    ps += p;
+                }
+            l[qb] = ps;
+        }
+#pragma unroll
+        for (int j = 0; j < BN / KSTEP; ++j)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                u32x4 pw;
+                pw[0] = pack2(sc[qb][2 * j][0], sc[qb][2 * j][1]);
+                pw[1] = pack2(sc[qb][2 * j][2], sc[qb][2 * j][3]);
+                pw[2] = pack2(sc[qb][2 * j + 1][0], sc[qb][2 * j + 1][1]);
+                pw[3] = pack2(sc[qb][2 * j + 1][2], sc[qb][2 * j + 1][3]);
+                pf[j][qb] = __builtin_bit_cast(bf16x8, pw);
+            }
+    };
+#endif
+#if PINGPONG
+    (void)compute;
+#define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | ((((n) >> 4) & 3) << 14) | (7 << 4) | (15 << 8))
+    // Ping-pong.  Waves i and i + 4 share a SIMD and belong to different
+    // splits.  Run in step, both multiply, then both exponentiate, and the
+    // matrix and vector pipes take turns (for 32 queries and 64 keys of 128:
+    // 1024 matrix cycles and about as many vector ones per wave and tile, one
+    // after the other).  Here split 1 runs one slot behind split 0: each
+    // slot, ended by a workgroup barrier, holds one split's softmax of its
+    // tile i (vector work) and the other's O^T += V^T P^T of tile i followed
+    // by S^T = K Q^T of tile i + 1 (matrix work).
+    //   Ring: the split's tile i has K and V in its slot i % 2.  After the
+    // matrix slot that reads V of tile i - 1 and K of tile i, the softmax
+    // slot of tile i loads K of tile i + 2 and V of tile i + 1 into the places
+    // just read, and waits for the loads of the softmax slot before it (K of
+    // tile i + 1, V of tile i), which the next matrix slot reads: a load has
+    // three slots to land.  The loads (16 address
+    // cycles each, for four waves) are spread between the exponentials: in
+    // one burst they held up the softmax for their whole length.
+    //   Loads past the last tile fetch that tile again, so that every slot
+    // issues the same number; nothing reads them.
+    // 1 x 24 x 4096 x 128, 128 x 64 tiles: 203.5 us in step, 197.7 with the
+    // reduction of the row maximum left to the tiles that move it (rescale),
+    // 188 in turns (1.10 PFLOP/s).  One workgroup a CU only: two of 64 KiB
+    // already fill each other's gaps (causal 1 x 32 x 1024 x 128: 17.6 us in
+    // step, 18.0 in turns; causal 2 x 16 x 777 x 64: 9.1 and 10.6).
+    constexpr int NKS = AD / KSTEP, NPJ = BN / KSTEP, NKF = KB * NKS, NVF = NPJ * DB;
+    constexpr int AHEAD = 8;                   // fragments read ahead of their MFMAs (divides NVF)
+    bf16_t *const Kr = ring[sp], *const Vr = ring[RING + sp];
+    auto slot_of = [&](int it) { return (it & 1) * SPLITS * KT_ELEMS; };
+    auto live = [&](int it) { return SPLITS * it + sp < n_kt && !skipped(SPLITS * it + sp); };
+    auto read_kf = [&](auto fc, const bf16_t *Ks) __attribute__((always_inline)) {
+        constexpr int f = decltype(fc)::value;
+        return *(const bf16x8 *)(Ks + (f / NKS) * MF * AD + koff[f % NKS]);
+    };
+    auto read_vf = [&](auto fc, const bf16_t *Vt) __attribute__((always_inline)) {
+        constexpr int f = decltype(fc)::value;
+        const bf16_t *const vp = Vt + voff[f % DB] + 32 * (f / DB) * AD;
+        const v4i16 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4p)(vp));
+        const v4i16 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4p)(vp + 16 * AD));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    static_assert(NVF % AHEAD == 0 && NKF >= AHEAD, "fragment ring");
+    accT sc[QB][KB];
+    bf16x8 pf[NPJ][QB], fr[AHEAD];
+    // S^T of a tile: its first AHEAD fragments are in fr
+    auto qk = [&](const bf16_t *Ks) __attribute__((always_inline)) {
+        seq<0, NKF>([&](auto fc) __attribute__((always_inline)) {
+            constexpr int f = decltype(fc)::value, kb = f / NKS, ks = f % NKS;
+            const bf16x8 x = fr[f % AHEAD];
+            if constexpr (f + AHEAD < NKF) fr[f % AHEAD] = read_kf(IntC<f + AHEAD>{}, Ks);
+            seq<0, QB>([&](auto qc) __attribute__((always_inline)) {
+                constexpr int qb = decltype(qc)::value;
+                sc[qb][kb] = mfma(x, qf[qb][ks], ks == 0 ? accT{} : sc[qb][kb]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // O^T += V^T P^T of a tile, its first AHEAD fragments in fr, reading the
+    // first fragments of K tile Kn
+    auto pv = [&](const bf16_t *Vt, const bf16_t *Kn) __attribute__((always_inline)) {
+        seq<0, NVF>([&](auto fc) __attribute__((always_inline)) {
+            constexpr int f = decltype(fc)::value, j = f / DB, db = f % DB;
+            const bf16x8 x = fr[f % AHEAD];
+            if constexpr (f + AHEAD < NVF) fr[f % AHEAD] = read_vf(IntC<f + AHEAD>{}, Vt);
+            else fr[f % AHEAD] = read_kf(IntC<f + AHEAD - NVF>{}, Kn);
+            seq<0, QB>([&](auto qc) __attribute__((always_inline)) {
+                constexpr int qb = decltype(qc)::value;
+                o[qb][db] = mfma(x, pf[j][qb], o[qb][db]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // softmax slot of tile it: the part between the row maximum and the end,
+    // in KB x QB groups of exponentials with a share of the loads in each
+    auto exps = [&](int it, auto act) __attribute__((always_inline)) {
+        const int kk = min(SPLITS * (it + 2) + sp, n_kt - 1), kv = min(SPLITS * (it + 1) + sp, n_kt - 1);
+        const unsigned lk = KA(SPLITS * (it & 1) + sp), lv = VA(SPLITS * ((it + 1) & 1) + sp);
+        seq<0, KB * QB>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int g = decltype(gc)::value, kb = g / QB, qb = g % QB;
+            constexpr int d0 = g * 2 * WL / (KB * QB), d1 = (g + 1) * 2 * WL / (KB * QB);
+            if constexpr (d0 < WL) gload_op(args.K, k_src, kk, lk, d0, d1 < WL ? d1 : WL);
+            if constexpr (d1 > WL) gload_op(args.V, v_src, kv, lv, d0 > WL ? d0 - WL : 0, d1 - WL);
+            if constexpr (decltype(act)::value) {
+                float p[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[qb][kb][r], SCALE_LOG2, -m[qb]));
+                l[qb] += (p[0] + p[1]) + (p[2] + p[3]);
+                u32x4 w = __builtin_bit_cast(u32x4, pf[kb / 2][qb]);
+                w[2 * (kb % 2)] = pack2(p[0], p[1]);
+                w[2 * (kb % 2) + 1] = pack2(p[2], p[3]);
+                pf[kb / 2][qb] = __builtin_bit_cast(bf16x8, w);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto slot_end = [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave's LDS reads are done
+        asm volatile("s_barrier" ::: "memory");
+    };
+    if (sp == 1) slot_end();
+    if (live(0)) {
+        seq<0, AHEAD>([&](auto f) __attribute__((always_inline)) { fr[decltype(f)::value] = read_kf(f, Kr); });
+        qk(Kr);
+    }
+    slot_end();
+#pragma nounroll
+    for (int it = 0; it < n_it; ++it) {
+        const int kt = SPLITS * it + sp, s0 = slot_of(it), s1 = slot_of(it + 1);
+        // softmax slot
+        const bool act = live(it);
+        if (act) {
+            float mx[QB];
+            if (needs_mask(kt)) mask(kt, sc);
+            tile_max(sc, mx);
+            rescale_all(mx);
+            exps(it, IntC<1>{});
+        } else {
+            exps(it, IntC<0>{});
+        }
+        WAIT_VM(2 * WL);           // the loads of the softmax slot before this one have landed
+        slot_end();
+        // matrix slot: its waves go first at the issue port
+        __builtin_amdgcn_s_setprio(2);
+        if (act) {
+            seq<0, AHEAD>([&](auto f) __attribute__((always_inline)) { fr[decltype(f)::value] = read_vf(f, Vr + s0); });
+            pv(Vr + s0, Kr + s1);
+            if (live(it + 1)) qk(Kr + s1);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        slot_end();
+    }
+    WAIT_VM(0);
+    if (sp == 0) slot_end();
+    __syncthreads();           // every wave is done with the ring (reused below)
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) l[qb] = group_sum(l[qb]);
+#undef WAIT_VM
+#elif STAGES == 4 && SPLITS > 1
     (void)compute;
 #define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | ((((n) >> 4) & 3) << 14) | (7 << 4) | (15 << 8))
     // The splits share a ring of 2 x SPLITS slots: iteration i computes tile
@@ -804,83 +1028,6 @@ void rc_attention(AttnArgs args) {
     constexpr int V1_PER = (VALU1 + MF1 - 1) / MF1;
     constexpr int DS1 = KB * NKS + 2 * NPJ * DB;            // phase-1 LDS reads
     constexpr int DS1_PER = (DS1 - KB * NKS + MF1 - 1) / MF1;
-    typedef short v4i16 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) v4i16 *lds_v4p;
-    auto needs_mask = [&](int kt) {
-#if CAUSAL
-        return (kt0 + kt) * BN + BN - 1 > q0w;
-#else
-        return RAGGED_S && (kt0 + kt) * BN + BN > AS;
-#endif
-    };
-    auto mask = [&](int kt, accT (&sc)[QB][KB]) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-#if CAUSAL
-            const int q = q0w + qb * MF + lane % MF;
-#else
-            const int q = AS - 1;      // keys past the sequence
-#endif
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int r = 0; r < ACCN; ++r)
-                    if ((kt0 + kt) * BN + kb * MF + key_of(r, lane) > q) sc[qb][kb][r] = -__builtin_inff();
-        }
-    };
-    // row maximum of a tile in log2 units, identical on every lane of a query
-    auto tile_max = [&](const accT (&sc)[QB][KB], float (&mx)[QB]) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float v = -__builtin_inff();
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int r = 0; r < ACCN; ++r) v = fmaxf(v, sc[qb][kb][r]);
-            mx[qb] = group_max(v) * SCALE_LOG2;
-        }
-    };
-    auto rescale = [&](const float (&mx)[QB]) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-            if (__builtin_amdgcn_ballot_w64(mx[qb] > m[qb] + RESCALE_LOG2) != 0) {
-                const float mnew = fmaxf(m[qb], mx[qb]);
-                const float alpha = __builtin_amdgcn_exp2f(m[qb] - mnew);
-                l[qb] *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int r = 0; r < ACCN; ++r) o[qb][db][r] *= alpha;
-                m[qb] = mnew;
-            }
-    };
-    // probabilities of a tile, packed into the P^T fragments of the P V product
-    auto probs = [&](accT (&sc)[QB][KB], bf16x8 (&pf)[NPJ][QB]) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float ps = l[qb];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int r = 0; r < ACCN; ++r) {
-                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[qb][kb][r], SCALE_LOG2, -m[qb]));
-                    sc[qb][kb][r] = p;
-                    ps += p;
-                }
-            l[qb] = ps;
-        }
-#pragma unroll
-        for (int j = 0; j < NPJ; ++j)
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                u32x4 pw;
-                pw[0] = pack2(sc[qb][2 * j][0], sc[qb][2 * j][1]);
-                pw[1] = pack2(sc[qb][2 * j][2], sc[qb][2 * j][3]);
-                pw[2] = pack2(sc[qb][2 * j + 1][0], sc[qb][2 * j + 1][1]);
-                pw[3] = pack2(sc[qb][2 * j + 1][2], sc[qb][2 * j + 1][3]);
-                pf[j][qb] = __builtin_bit_cast(bf16x8, pw);
-            }
-    };
     auto read_k = [&](const bf16_t *Ks, bf16x8 (&kf)[KB][NKS]) {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
@@ -966,7 +1113,7 @@ void rc_attention(AttnArgs args) {
                     const bf16_t *vc, int fill) {
         if (j + 3 < n_loc) gload_lds(gt(j + 3), 4 * sp + fill);
         if (j < nact) {
-            rescale(mx);
+            rescale_all(mx);
             bf16x8 vf[NPJ][DB], pf[NPJ][QB];
             if (j + 1 < nact) {
                 if (needs_mask(gt(j + 1))) phase1(IntC<1>{}, gt(j + 1), cur, nxt, kn, vc, vf, pf);
@@ -1063,7 +1210,7 @@ void rc_attention(AttnArgs args) {
     }
 #endif
 
-#if STAGES != 5
+#if STAGES != 5 && !PINGPONG
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) l[qb] = group_sum(l[qb]);
 #endif

@@ -77,6 +77,7 @@ struct Source {
     const char *file;     // kernel source text
     const char *entry;    // kernel function name
     std::string defines;  // generated prologue
+    std::string fallback; // further definitions, should the kernel spill without them
 };
 
 std::mutex g_mu;
@@ -343,19 +344,17 @@ rc_status check_spill(const std::vector<char> &code, const char *entry) {
     return RC_OK;
 }
 
-std::string def(const char *name, long long v);
-
-// The code object of a kernel.  The ring GEMMs (stages 7) pin the order of
-// their loads, fragment reads and MFMAs, which a few variants at the register
-// limit cannot hold without spilling; those are compiled again with the order
-// left to the compiler.  `status` of check_spill on the returned code.
+// The code object of a kernel.  A few variants at the register limit cannot
+// hold the pinned instruction order of their kernel without spilling; those
+// are compiled again with the source's fallback definitions.  `spill`:
+// check_spill of the returned code.
 rc_status build_kernel(const Source &s, std::vector<char> &code, std::string &key, rc_status &spill) {
     rc_status r = compile(s, code, key);
     if (r != RC_OK) return r;
     spill = check_spill(code, s.entry);
-    if (spill != RC_ERR_ILLEGAL_SCHEDULE || s.defines.find("#define NSTAGE ") == std::string::npos) return RC_OK;
+    if (spill != RC_ERR_ILLEGAL_SCHEDULE || s.fallback.empty()) return RC_OK;
     Source f = s;
-    f.defines += def("RING_FREE", 1);
+    f.defines += s.fallback;
     r = compile(f, code, key);
     if (r != RC_OK) return r;
     spill = check_spill(code, s.entry);
@@ -799,6 +798,10 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
             break;
         }
         default: return fail(RC_ERR_UNSUPPORTED, "unknown operator kind");
+    }
+    for (auto &k : p.kerns) {
+        if (k.src.defines.find("#define NSTAGE ") != std::string::npos) k.src.fallback = def("RING_FREE", 1);
+        if (k.src.file == SRC_attention) k.src.fallback = def("PINGPONG", 0);
     }
     p.workspace = ws.total;
     p.parts = ws.parts;

@@ -518,6 +518,30 @@ def ring_edge_jobs():
             for b in RING_EDGE_BLOCKS for n in RING_EDGE_TILES]
 
 
+# Attention whose two key splits take turns on the matrix cores (one
+# workgroup per CU: block_n x head dim of 8192): 1 to 5 key tiles, so that a
+# split has none, one or a few, with and without a partial last tile; one and
+# two query blocks a wave; every head dimension that admits it; work items of
+# 4 key tiles.
+PINGPONG_ATTN = [(d, bn, s, bm, causal, chunk)
+                 for d, bn in ((128, 64), (64, 128), (256, 32))
+                 for tiles, extra in ((1, 0), (1, 9), (2, 0), (3, 1), (4, 0), (5, 30))
+                 for s in (bn * tiles + extra,)
+                 for bm in (64, 128) if d < 256 or bm == 64
+                 for causal in (0, 1) for chunk in ((0, 4) if tiles == 5 else (0,))]
+
+
+def pingpong_jobs():
+    jobs = []
+    for d, bn, s, bm, causal, chunk in PINGPONG_ATTN:
+        op = rc.Op(rc.RC_OP_ATTENTION, (1, 2, s, d), causal)
+        sched = op.from_string(f"block_m={bm},block_n={bn},waves=4,mfma=16,stages=4,vec=8,unroll=1,order=1,occ=1,"
+                               f"splits=2,chunk={chunk}")
+        if sched.validate() == "":          # a block twice the sequence is refused
+            jobs.append((op, str(sched)))
+    return jobs
+
+
 # fp32 ring (stages 2, 16-byte vectors, whole 16-row blocks of K): K of one
 # tile and less, around the ring's four buffers, and a last tile of one
 # vector; rows and columns past the edges; both layouts of B; every tile_n
@@ -586,7 +610,7 @@ def all_compile_jobs():
     op = rc.Op(rc.RC_OP_CONV2D, W.workload_op("conv3x3_n2_64x64_c320_k320").dims, rc.RC_FLAG_NO_ACT)
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
-    for op, text in ring_edge_jobs() + gemm_ring_jobs():
+    for op, text in ring_edge_jobs() + gemm_ring_jobs() + pingpong_jobs():
         jobs.append((op, [op.from_string(text)]))
     for kind, big, small, flags, text in NOALLOC_PAIRS:
         for dims in (big, small):

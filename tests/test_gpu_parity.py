@@ -100,6 +100,18 @@ def test_small_shapes(key, sched_text):
     assert_parity(op, y, host, label=f"{key} {sched_text}")
 
 
+@pytest.mark.parametrize("job", range(len(cases.pingpong_jobs())))
+def test_attention_splits_in_turns(job):
+    # Keys that grow along the sequence (to 8 times their size) move the
+    # running maximum again and again, by more than the lazy rescale's 2^8.
+    op, text = cases.pingpong_jobs()[job]
+    host = W.host_inputs(op, seed=3)
+    ramp = np.linspace(0.25, 8.0, op.dims[2], dtype=np.float32)[None, None, :, None]
+    host["K"] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(host["K"]) * ramp)
+    y, _ = run(op, op.from_string(text), host)
+    assert_parity(op, y, host, label=f"{op.dims} {text}")
+
+
 def test_gemm_sweep_has_18_legal_points():
     op = cases.small_op("gemm")
     legal = [s for s in cases.gemm_sweep() if op.from_string(s).validate() == ""]
