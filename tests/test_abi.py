@@ -296,3 +296,20 @@ def test_convolution_with_no_output_pixel_has_no_schedule():
     with pytest.raises(rc.RCError) as e:
         op.default()
     assert e.value.status == rc.RC_ERR_UNSUPPORTED and "empty output" in str(e.value)
+
+
+def test_launch_packs_the_same_argument_block():
+    # Plan.launch passes its rc_args as packed bytes: the same bytes as the
+    # structure, for every number of inputs, missing ones included.
+    class Tensor:
+        def __init__(self, p):
+            self.p = p
+
+        def data_ptr(self):
+            return self.p
+
+    for n in range(9):
+        ins = [Tensor((1 << 47) + 16 * i) if i % 3 else None for i in range(n)]
+        assert rc._pack_args(iter(ins), Tensor(4096)) == bytes(rc.Plan._args(ins, Tensor(4096)))
+    with pytest.raises(IndexError):
+        rc._pack_args([None] * 9, None)
