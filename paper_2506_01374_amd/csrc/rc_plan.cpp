@@ -652,7 +652,8 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
             kh.bind = [=](const rc_args *a, char *w, ArgBlob &b) {
                 put(b, MoeHistArgs{a->in[1], w + offCnt});
             };
-            p.kerns.push_back(kh);
+            // one block of rows: the scatter kernel counts them itself
+            if (nblk > 1) p.kerns.push_back(kh);
             Kern k0;
             k0.src = Source{SRC_aux, "rc_moe_prep", moe};
             k0.grid = dim3((unsigned)nblk, 1, 1);
@@ -675,8 +676,8 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
                                     fuse ? nullptr : w + offU, nullptr, w + offPerm, w + offOff,
                                     w + offTu});
             };
+            p.dominant = (int)p.kerns.size();
             p.kerns.push_back(k1);
-            p.dominant = 2;
             if (!fuse) {
                 Kern ke;
                 ke.src = Source{SRC_aux, "rc_swiglu_f32", def("EW_N", R * I) + def("EW_COLS", I)};

@@ -587,6 +587,12 @@ NOALLOC_PAIRS = [
 ]
 
 
+# MoE routing around one block of 1,024 routed rows (one block: the scatter
+# kernel counts the rows itself), top-1 and top-2.
+PREP_EDGE_DIMS = [(1, 256, 8, 128, 1), (1023, 256, 8, 128, 1), (1024, 256, 8, 128, 1), (1025, 256, 8, 128, 1),
+                  (512, 256, 8, 128, 2), (513, 256, 8, 128, 2)]
+
+
 def walk_compile_jobs():
     """(op, [schedules]) of the random-walk cases; some may spill (rejected
     at compile time, which the tests accept)."""
@@ -616,6 +622,9 @@ def all_compile_jobs():
         for dims in (big, small):
             op = rc.Op(kind, dims, flags)
             jobs.append((op, [op.from_string(text)]))
+    for dims in PREP_EDGE_DIMS:
+        op = rc.Op(rc.RC_OP_MOE, dims)
+        jobs.append((op, [op.from_string(SCHEDULES["moe"][1])]))
     moe = W.workload_op("moe_t4096_h2048_e64_i1408_top6")
     for dims in ((256, 256, 8, 128, 2), (256, 256, 8, 128, 1), (8192, 256, 64, 128, 6)):
         op = rc.Op(rc.RC_OP_MOE, dims)

@@ -113,6 +113,22 @@ def test_moe_prep_bitexact_edge_routings(pattern):
             assert ok, worst
 
 
+@pytest.mark.parametrize("dims", cases.PREP_EDGE_DIMS)
+def test_moe_prep_bitexact_around_one_block(dims):
+    T, Hd, E, I, k = dims
+    op = rc.Op(rc.RC_OP_MOE, dims)
+    sched = op.from_string(cases.SCHEDULES["moe"][1])
+    host = W.host_inputs(op, seed=4)
+    plan, dev, out, ws = launch(op, sched, host)
+    _check_prep(op, sched, host, plan, ws)
+    rows = host["ids"].reshape(-1)
+    nblk = -(-rows.size // 1024)
+    assert plan.nkernels == (5 if nblk > 1 else 4) and plan.dominant == plan.nkernels - 3
+    counts = ws_int32(plan, ws, "block_counts").reshape(nblk, E)
+    for b in range(nblk):
+        assert np.array_equal(counts[b], np.bincount(rows[1024 * b:1024 * (b + 1)], minlength=E))
+
+
 def test_moe_full_size_last_tile_of_every_expert():
     # Full-size MoE output on the tokens owning the first and last row of
     # every expert's last M tile in both expert GEMMs (the partially filled
