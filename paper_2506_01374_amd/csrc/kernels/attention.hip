@@ -367,6 +367,31 @@ void rc_attention(AttnArgs args) {
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :: "v"(off), "s"(gbase), "s"(lds_addr) : "memory", "m0");
     };
+    // tile kt into ring buffer b
+    auto gload_lds = [&](int kt, int b) {
+        const bf16_t *Kg = args.K + base + (size_t)(kt0 + kt) * BN * AD;
+        const bf16_t *Vg = args.V + base + (size_t)(kt0 + kt) * BN * AD;
+        const int kvalid = AS - (kt0 + kt) * BN;     // wave-uniform
+        if (RAGGED_S && kvalid < BN) {
+            // last, partial tile: rows past the sequence fetch its last row
+#pragma unroll
+            for (int j = 0; j < WL; ++j) {
+                const unsigned back = 2u * AD * (unsigned)max(kv_row[RAGGED_S ? j : 0] - (kvalid - 1), 0);
+                dma(Kg, k_src[j] - back, KA(b) + j * 1024u);
+            }
+#pragma unroll
+            for (int j = 0; j < WL; ++j) {
+                const unsigned back = 2u * AD * (unsigned)max(kv_row[RAGGED_S ? j : 0] - (kvalid - 1), 0);
+                dma(Vg, v_src[j] - back, VA(b) + j * 1024u);
+            }
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < WL; ++j) dma(Kg, k_src[j], KA(b) + j * 1024u);
+#pragma unroll
+        for (int j = 0; j < WL; ++j) dma(Vg, v_src[j], VA(b) + j * 1024u);
+    };
+#if PINGPONG
     // this wave's loads j0 .. j1 - 1 of K (or V) of tile kt to LDS address lds
     auto gload_op = [&](const bf16_t *src, const unsigned (&off)[WL], int kt, unsigned lds, int j0, int j1)
                         __attribute__((always_inline)) {
@@ -384,10 +409,7 @@ void rc_attention(AttnArgs args) {
 #pragma unroll
         for (int j = j0; j < j1; ++j) dma(g, off[j], lds + j * 1024u);
     };
-    auto gload_lds = [&](int kt, int b) {
-        gload_op(args.K, k_src, kt, KA(b), 0, WL);
-        gload_op(args.V, v_src, kt, VA(b), 0, WL);
-    };
+#endif
 #if STAGES == 5
     // split sp's first three tiles (sp, sp + SPLITS, sp + 2 SPLITS) are in
     // flight while Q is read, in the split's slots 4 sp .. 4 sp + 2
@@ -402,7 +424,9 @@ void rc_attention(AttnArgs args) {
 #else
     // split sp's first tile (tile sp) is in flight while Q is read
     if (sp < n_kt) gload_lds(sp, sp);
-    if (PINGPONG && SPLITS + sp < n_kt) gload_op(args.K, k_src, SPLITS + sp, KA(SPLITS + sp), 0, WL);
+#if PINGPONG
+    if (SPLITS + sp < n_kt) gload_op(args.K, k_src, SPLITS + sp, KA(SPLITS + sp), 0, WL);
+#endif
 #endif
 #endif
     bf16x8 qf[QB][AD / KSTEP];
