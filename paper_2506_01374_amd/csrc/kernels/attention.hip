@@ -836,7 +836,7 @@ void rc_attention(AttnArgs args) {
     // issues the same number; nothing reads them.
     // 1 x 24 x 4096 x 128, 128 x 64 tiles: 203.5 us in step, 197.7 with the
     // reduction of the row maximum left to the tiles that move it (rescale),
-    // 188 in turns (1.10 PFLOP/s).  One workgroup a CU only: two of 64 KiB
+    // 182 in turns (1.13 PFLOP/s).  One workgroup a CU only: two of 64 KiB
     // already fill each other's gaps (causal 1 x 32 x 1024 x 128: 17.6 us in
     // step, 18.0 in turns; causal 2 x 16 x 777 x 64: 9.1 and 10.6).
     constexpr int NKS = AD / KSTEP, NPJ = BN / KSTEP, NKF = KB * NKS, NVF = NPJ * DB;
