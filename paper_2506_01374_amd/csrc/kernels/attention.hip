@@ -34,6 +34,8 @@
 //                state (O, m, l) in the workspace and rc_attention_combine
 //                merges them, which shortens the longest workgroup's chain
 //                of dependent key tiles
+//   PINGPONG     1: the two key splits take turns on the matrix cores (chosen
+//                from the schedule and the sizes where it pays)
 //   AB AH AS AD  batch, heads, sequence length, head dim.  AS need not be a
 //                multiple of BM or BN: the last query tile's rows past AS
 //                read row AS - 1 of Q and are not stored; the last key
@@ -63,11 +65,13 @@
 // direct-to-LDS paths: ring slots per operand (two per split with several
 // splits)
 #define RING (STAGES == 5 ? 4 * SPLITS : SPLITS > 1 ? 2 * SPLITS : 3)
-// Two key splits of four waves each whose ring (4 RING BN AD bytes) leaves room
-// for one workgroup per CU take turns on the matrix cores (measured below)
-#ifndef PINGPONG
-#define PINGPONG (STAGES == 4 && SPLITS == 2 && NW == 4 && 4 * RING * BN * AD > 81920)
-#endif
+// The row maximum is reduced across lanes for tiles that move it only (see
+// rescale), except in these variants, which need the registers that the
+// compiler then takes: 1 x 24 x 4096 x 64, causal, in 64 x 32 tiles has five
+// waves per SIMD instead of four (87.3 us; 94.0 when reduced only where it
+// moves), and head dimension 256 would spill.  With few workgroups the fifth
+// wave is not there anyway (1 x 32 x 1024 x 64: 19.3 and 17.9 us).
+#define EAGER_MAX (CAUSAL && STAGES == 4 && SPLITS == 1 && BN == 32 && !RAGGED_S && (AD == 256 || AB * AH * NQT > 512))
 #define KB (BN / MF)
 #define DB (AD / MF)
 #define NQT ((AS + BM - 1) / BM)
@@ -448,10 +452,10 @@ void rc_attention(AttnArgs args) {
 #endif
 
     accT o[QB][DB];
-    float m[QB], l[QB], vlim[QB];      // vlim: the score past which m moves
+    float m[QB], l[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        m[qb] = vlim[qb] = -__builtin_inff();
+        m[qb] = -__builtin_inff();
         l[qb] = 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -471,10 +475,13 @@ void rc_attention(AttnArgs args) {
     // Moves the running maximum (and rescales O and l) if some lane's largest
     // score lies past the limit.  A query's maximum is past it exactly when
     // one of its lanes' is, so the reduction across the lanes of a query,
-    // a chain of swaps and waits, is left to the tiles that do move it.
+    // a chain of swaps and waits, is left to the tiles that do move it.  The
+    // limit is formed from m anew each time: held, it costs every path a
+    // register per query block, and some variants at their limit then spill.
     auto rescale = [&](int qb, float v) __attribute__((always_inline)) {
-        if (__builtin_amdgcn_ballot_w64(v > vlim[qb]) != 0) {
-            const float mnew = fmaxf(m[qb], group_max(v) * SCALE_LOG2);
+        if (EAGER_MAX) v = group_max(v);
+        if (__builtin_amdgcn_ballot_w64(v * SCALE_LOG2 > m[qb] + RESCALE_LOG2) != 0) {
+            const float mnew = fmaxf(m[qb], (EAGER_MAX ? v : group_max(v)) * SCALE_LOG2);
             const float alpha = __builtin_amdgcn_exp2f(m[qb] - mnew);
             l[qb] *= alpha;
 #pragma unroll
@@ -482,7 +489,6 @@ void rc_attention(AttnArgs args) {
 #pragma unroll
                 for (int r = 0; r < ACCN; ++r) o[qb][db][r] *= alpha;
             m[qb] = mnew;
-            vlim[qb] = (mnew + RESCALE_LOG2) * (1.0f / SCALE_LOG2);
         }
     };
 

@@ -768,6 +768,10 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
             long wslot = qb * 2 * mf + qb * (Dh / mf) * accn * 64;
             size_t offP = chunk > 0 ? ws.add((size_t)B * Hh * nqt * maxch * w * wslot * 4, "partials") : 0;
             Kern k;
+            // Two key splits of four waves each whose ring (16 bn Dh bytes)
+            // leaves room for one workgroup per CU take turns on the matrix
+            // cores.
+            const bool turns = kv(d, s, "stages") == 4 && kv(d, s, "splits") == 2 && w == 4 && 16ll * bn * Dh > 81920;
             double scale_log2 = 1.4426950408889634 / std::sqrt((double)Dh);
             char sbuf[64];
             snprintf(sbuf, sizeof sbuf, "#define SCALE_LOG2 %.17gf\n", scale_log2);
@@ -779,7 +783,7 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
                                def("SPLITS", kv(d, s, "splits")) + def("CHUNK", chunk) +
                                def("AB", B) + def("AH", Hh) +
                                def("AS", S) + def("AD", Dh) +
-                               def("CAUSAL", causal ? 1 : 0) + sbuf};
+                               def("CAUSAL", causal ? 1 : 0) + def("PINGPONG", turns) + sbuf};
             k.grid = dim3((unsigned)(B * Hh * items), 1, 1);
             k.block = dim3(64 * w * kv(d, s, "splits"), 1, 1);
             k.flops = rc_op_flops(d);
@@ -802,7 +806,9 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
     }
     for (auto &k : p.kerns) {
         if (k.src.defines.find("#define NSTAGE ") != std::string::npos) k.src.fallback = def("RING_FREE", 1);
-        if (k.src.file == SRC_attention) k.src.fallback = def("PINGPONG", 0);
+        // (only where it changes the source: a spilled variant is not compiled twice to the same code)
+        if (k.src.defines.find("#define PINGPONG 1") != std::string::npos)
+            k.src.fallback = "#undef PINGPONG\n" + def("PINGPONG", 0);
     }
     p.workspace = ws.total;
     p.parts = ws.parts;

@@ -542,6 +542,23 @@ def pingpong_jobs():
     return jobs
 
 
+# Attention variants at the limit of their registers (a register more in the
+# loop and they spill): each has to compile.
+TIGHT_ATTN = [
+    ((1, 2, 1000, 128), 1, "block_m=128,block_n=64,waves=8,mfma=16,stages=4,vec=8,unroll=2,order=2,occ=1,splits=2,chunk=4"),
+    ((1, 2, 1000, 128), 1, "block_m=256,block_n=128,waves=8,mfma=16,stages=2,vec=8,unroll=1,order=0,occ=1,splits=1,chunk=0"),
+    ((1, 4, 777, 64), 1, "block_m=128,block_n=32,waves=4,mfma=16,stages=2,vec=8,unroll=2,order=0,occ=4,splits=2,chunk=8"),
+    ((1, 4, 1000, 128), 1, "block_m=128,block_n=64,waves=8,mfma=16,stages=4,vec=8,unroll=1,order=1,occ=4,splits=2,chunk=4"),
+    ((1, 2, 300, 256), 0, "block_m=64,block_n=32,waves=2,mfma=16,stages=2,vec=8,unroll=2,order=0,occ=1,splits=2,chunk=8"),
+    ((1, 2, 300, 256), 0, "block_m=64,block_n=32,waves=2,mfma=32,stages=1,vec=4,unroll=1,order=0,occ=1,splits=2,chunk=8"),
+    ((1, 2, 1000, 256), 1, "block_m=128,block_n=32,waves=4,mfma=16,stages=3,vec=4,unroll=2,order=0,occ=1,splits=1,chunk=16"),
+    ((1, 2, 1000, 256), 1, "block_m=128,block_n=64,waves=4,mfma=16,stages=1,vec=8,unroll=2,order=1,occ=1,splits=1,chunk=0"),
+] + [
+    ((1, 2, 2048, 256), 1, f"block_m={32 * w},block_n=32,waves={w},mfma=16,stages=4,vec=8,unroll=1,order=1,occ=1,splits=1,chunk=0")
+    for w in (1, 2, 4)
+]
+
+
 # fp32 ring (stages 2, 16-byte vectors, whole 16-row blocks of K): K of one
 # tile and less, around the ring's four buffers, and a last tile of one
 # vector; rows and columns past the edges; both layouts of B; every tile_n
@@ -617,6 +634,9 @@ def all_compile_jobs():
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
     for op, text in ring_edge_jobs() + gemm_ring_jobs() + pingpong_jobs():
+        jobs.append((op, [op.from_string(text)]))
+    for dims, flags, text in TIGHT_ATTN:
+        op = rc.Op(rc.RC_OP_ATTENTION, dims, flags)
         jobs.append((op, [op.from_string(text)]))
     for kind, big, small, flags, text in NOALLOC_PAIRS:
         for dims in (big, small):

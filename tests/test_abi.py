@@ -13,6 +13,8 @@ import pytest
 from paper_2506_01374_amd import rc
 from paper_2506_01374_amd import workloads as W
 
+import cases
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -296,6 +298,33 @@ def test_convolution_with_no_output_pixel_has_no_schedule():
     with pytest.raises(rc.RCError) as e:
         op.default()
     assert e.value.status == rc.RC_ERR_UNSUPPORTED and "empty output" in str(e.value)
+
+
+@pytest.mark.parametrize("job", range(len(cases.TIGHT_ATTN)))
+def test_attention_at_its_register_limit_compiles(job):
+    dims, flags, text = cases.TIGHT_ATTN[job]
+    rc.set_cache_dir(os.path.join(ROOT, "paper_2506_01374_amd", "jit_cache"))
+    op = rc.Op(rc.RC_OP_ATTENTION, dims, flags)
+    sched = op.from_string(text)
+    assert sched.validate() == ""
+    assert rc.precompile(op, [sched], 1) == [rc.RC_OK]
+
+
+def _objects(tmp_path, op, text, entry):
+    """Status of a schedule compiled into an empty cache, and the number of
+    code objects of `entry` that it took (a second one: the fallback)."""
+    rc.set_cache_dir(str(tmp_path))
+    try:
+        st = rc.precompile(op, [op.from_string(text)], 1)[0]
+    finally:
+        rc.set_cache_dir(os.path.join(ROOT, "paper_2506_01374_amd", "jit_cache"))
+    return st, len([f for f in os.listdir(tmp_path) if f.startswith(entry + "_") and f.endswith(".hsaco")])
+
+
+def test_spilled_attention_is_compiled_once(tmp_path):
+    op = rc.Op(rc.RC_OP_ATTENTION, (1, 8, 1024, 128), rc.RC_FLAG_CAUSAL)
+    text = "block_m=32,block_n=64,waves=1,mfma=16,stages=2,vec=2,unroll=2,order=0,occ=1,splits=1,chunk=0"
+    assert _objects(tmp_path, op, text, "rc_attention") == (rc.RC_ERR_ILLEGAL_SCHEDULE, 1)
 
 
 def test_launch_packs_the_same_argument_block():
