@@ -294,6 +294,14 @@ typedef struct rc_kernel_info {
 rc_status rc_describe(const rc_op_desc *d, const rc_schedule *s, rc_kernel_info *buf,
                       int32_t cap, int32_t *n);
 
+/* The generated definitions ("#define NAME VALUE" lines) that kernel i of a
+ * schedule is built with: which variant of its source the rules chose, and
+ * whether it is the fallback for a variant that would spill (whose lines
+ * come last).  Compiles like rc_describe; needs no GPU.  Writes at most cap
+ * bytes, NUL-terminated; RC_ERR_INVALID_ARGUMENT for no such kernel. */
+rc_status rc_kernel_defines(const rc_op_desc *d, const rc_schedule *s, int32_t i, char *buf,
+                            size_t cap);
+
 typedef struct rc_args {
     uint32_t struct_size;
     const void *in[8];

@@ -347,17 +347,20 @@ rc_status check_spill(const std::vector<char> &code, const char *entry) {
 // The code object of a kernel.  A few variants at the register limit cannot
 // hold the pinned instruction order of their kernel without spilling; those
 // are compiled again with the source's fallback definitions.  `spill`:
-// check_spill of the returned code.
-rc_status build_kernel(const Source &s, std::vector<char> &code, std::string &key, rc_status &spill) {
+// check_spill of the returned code; `defines`: its definitions.
+rc_status build_kernel(const Source &s, std::vector<char> &code, std::string &key, rc_status &spill,
+                       std::string *defines = nullptr) {
     rc_status r = compile(s, code, key);
     if (r != RC_OK) return r;
     spill = check_spill(code, s.entry);
+    if (defines) *defines = s.defines;
     if (spill != RC_ERR_ILLEGAL_SCHEDULE || s.fallback.empty()) return RC_OK;
     Source f = s;
     f.defines += s.fallback;
     r = compile(f, code, key);
     if (r != RC_OK) return r;
     spill = check_spill(code, s.entry);
+    if (defines) *defines = f.defines;
     return RC_OK;
 }
 
@@ -948,6 +951,24 @@ rc_status rc_describe(const rc_op_desc *d, const rc_schedule *s, rc_kernel_info 
         k.waves_per_simd = std::min(by_regs, by_lds);
         buf[i] = k;
     }
+    return RC_OK;
+}
+
+rc_status rc_kernel_defines(const rc_op_desc *d, const rc_schedule *s, int32_t i, char *buf, size_t cap) {
+    if (!desc_ok(d) || !s || !buf || cap == 0) return fail(RC_ERR_INVALID_ARGUMENT, "bad arguments");
+    std::string why = check_schedule(d, s);
+    if (!why.empty()) return fail(RC_ERR_ILLEGAL_SCHEDULE, why);
+    rc_plan p;
+    rc_status r = describe(d, s, p);
+    if (r != RC_OK) return r;
+    if (i < 0 || i >= (int32_t)p.kerns.size()) return fail(RC_ERR_INVALID_ARGUMENT, "no such kernel");
+    std::vector<char> code;
+    std::string key, defines;
+    rc_status spill = RC_OK;
+    r = build_kernel(p.kerns[i].src, code, key, spill, &defines);
+    if (r != RC_OK) return r;
+    if (spill != RC_OK) return spill;
+    snprintf(buf, cap, "%s", defines.c_str());
     return RC_OK;
 }
 

@@ -125,6 +125,8 @@ _SIGS = [
     ("rc_describe", ctypes.c_int, [ctypes.POINTER(rc_op_desc), ctypes.POINTER(rc_schedule),
                                    ctypes.POINTER(rc_kernel_info), ctypes.c_int32,
                                    ctypes.POINTER(ctypes.c_int32)]),
+    ("rc_kernel_defines", ctypes.c_int, [ctypes.POINTER(rc_op_desc), ctypes.POINTER(rc_schedule),
+                                         ctypes.c_int32, ctypes.c_char_p, ctypes.c_size_t]),
     ("rc_plan_create", ctypes.c_int, [ctypes.POINTER(rc_op_desc), ctypes.POINTER(rc_schedule),
                                       ctypes.POINTER(ctypes.c_void_p)]),
     ("rc_plan_destroy", None, [ctypes.c_void_p]),
@@ -389,6 +391,14 @@ def describe(op: Op, sched: Schedule) -> List[dict]:
         out.append({f: (getattr(k, f).decode() if f == "name" else getattr(k, f))
                     for f, _ in rc_kernel_info._fields_ if f != "struct_size"})
     return out
+
+
+def kernel_defines(op: Op, sched: Schedule, i: int = 0) -> Dict[str, str]:
+    """Definitions that kernel i of a schedule is built with (no GPU)."""
+    buf = ctypes.create_string_buffer(8192)
+    _check(lib().rc_kernel_defines(op.ref, ctypes.byref(sched.raw), i, buf, 8192), "rc_kernel_defines")
+    return {w[1]: w[2] for w in (line.split(None, 2) for line in buf.value.decode().splitlines())
+            if len(w) == 3 and w[0] == "#define"}
 
 
 def set_cache_dir(path: Optional[str]) -> None:

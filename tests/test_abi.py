@@ -327,6 +327,18 @@ def test_spilled_attention_is_compiled_once(tmp_path):
     assert _objects(tmp_path, op, text, "rc_attention") == (rc.RC_ERR_ILLEGAL_SCHEDULE, 1)
 
 
+def test_kernel_defines():
+    op = rc.Op(rc.RC_OP_ATTENTION, (1, 24, 4096, 128))
+    sched = op.from_string(cases.TUNED["attention_noncausal_b1_h24_s4096_d128"])
+    d = rc.kernel_defines(op, sched)
+    assert (d["AS"], d["AD"], d["CAUSAL"], d["PINGPONG"]) == ("4096", "128", "0", "1")
+    buf = ctypes.create_string_buffer(8)
+    f = rc.lib().rc_kernel_defines
+    assert f(op.ref, ctypes.byref(sched.raw), 0, buf, 8) == rc.RC_OK and buf.value == b"#define"
+    for i in (-1, 1):
+        assert f(op.ref, ctypes.byref(sched.raw), i, buf, 8) == 1
+
+
 def test_launch_packs_the_same_argument_block():
     # Plan.launch passes its rc_args as packed bytes: the same bytes as the
     # structure, for every number of inputs, missing ones included.
