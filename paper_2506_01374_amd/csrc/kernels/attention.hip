@@ -396,23 +396,21 @@ void rc_attention(AttnArgs args) {
         for (int j = 0; j < WL; ++j) dma(Vg, v_src[j], VA(b) + j * 1024u);
     };
 #if PINGPONG
-    // this wave's loads j0 .. j1 - 1 of K (or V) of tile kt to LDS address lds
-    auto gload_op = [&](const bf16_t *src, const unsigned (&off)[WL], int kt, unsigned lds, int j0, int j1)
-                        __attribute__((always_inline)) {
+    // this wave's loads j0 .. j1 - 1 of tile kt of K (or V) to LDS address
+    // lds (gload_lds in parts that the splits in turns issue apart); `edge`: in the last, partial tile rows past the sequence fetch its
+    // last row
+    auto load_op = [&](const bf16_t *src, const unsigned (&off)[WL], int kt, unsigned lds, int j0, int j1,
+                       auto edge) __attribute__((always_inline)) {
         const bf16_t *g = src + base + (size_t)(kt0 + kt) * BN * AD;
-        const int kvalid = AS - (kt0 + kt) * BN;     // wave-uniform
-        if (RAGGED_S && kvalid < BN) {
-            // last, partial tile: rows past the sequence fetch its last row
+        const int last = AS - (kt0 + kt) * BN - 1;      // wave-uniform
 #pragma unroll
-            for (int j = j0; j < j1; ++j) {
-                const unsigned back = 2u * AD * (unsigned)max(kv_row[RAGGED_S ? j : 0] - (kvalid - 1), 0);
-                dma(g, off[j] - back, lds + j * 1024u);
-            }
-            return;
+        for (int j = j0; j < j1; ++j) {
+            unsigned o = off[j];
+            if constexpr (decltype(edge)::value) o -= 2u * AD * (unsigned)max(kv_row[RAGGED_S ? j : 0] - last, 0);
+            dma(g, o, lds + j * 1024u);
         }
-#pragma unroll
-        for (int j = j0; j < j1; ++j) dma(g, off[j], lds + j * 1024u);
     };
+    auto partial = [&](int kt) { return AS % BN != 0 && AS - (kt0 + kt) * BN < BN; };     // wave-uniform
 #endif
 #if STAGES == 5
     // split sp's first three tiles (sp, sp + SPLITS, sp + 2 SPLITS) are in
@@ -429,7 +427,10 @@ void rc_attention(AttnArgs args) {
     // split sp's first tile (tile sp) is in flight while Q is read
     if (sp < n_kt) gload_lds(sp, sp);
 #if PINGPONG
-    if (SPLITS + sp < n_kt) gload_op(args.K, k_src, SPLITS + sp, KA(SPLITS + sp), 0, WL);
+    if (SPLITS + sp < n_kt) {
+        if (partial(SPLITS + sp)) load_op(args.K, k_src, SPLITS + sp, KA(SPLITS + sp), 0, WL, IntC<1>{});
+        else load_op(args.K, k_src, SPLITS + sp, KA(SPLITS + sp), 0, WL, IntC<0>{});
+    }
 #endif
 #endif
 #endif
@@ -842,9 +843,10 @@ void rc_attention(AttnArgs args) {
     // issues the same number; nothing reads them.
     // 1 x 24 x 4096 x 128, 128 x 64 tiles: 203.5 us in step, 197.7 with the
     // reduction of the row maximum left to the tiles that move it (rescale),
-    // 182 in turns (1.13 PFLOP/s).  One workgroup a CU only: two of 64 KiB
-    // already fill each other's gaps (causal 1 x 32 x 1024 x 128: 17.6 us in
-    // step, 18.0 in turns; causal 2 x 16 x 777 x 64: 9.1 and 10.6).
+    // 182 in turns (1.13 PFLOP/s; a slower card 212 -> 192).  One workgroup a
+    // CU only: two of 64 KiB already fill each other's gaps (causal 1 x 32 x
+    // 1024 x 128: 17.6 us in step, 18.0 in turns; causal 2 x 16 x 777 x 64:
+    // 9.1 and 10.6), and only with key tiles enough (the host's rule).
     constexpr int NKS = AD / KSTEP, NPJ = BN / KSTEP, NKF = KB * NKS, NVF = NPJ * DB;
     constexpr int AHEAD = 8;                   // fragments read ahead of their MFMAs (divides NVF)
     bf16_t *const Kr = ring[sp], *const Vr = ring[RING + sp];
@@ -893,28 +895,44 @@ void rc_attention(AttnArgs args) {
         });
     };
     // softmax slot of tile it: the part between the row maximum and the end,
-    // in KB x QB groups of exponentials with a share of the loads in each
+    // in KB x QB groups of exponentials with a share of the loads in each;
+    // a slot that loads the sequence's partial tile issues its loads first
+    // (an edge check in each share: 1 x 12 x 3604 x 128, causal, 128 x 64 tiles,
+    // 57.1 us; one for the slot: 52.6)
     auto exps = [&](int it, auto act) __attribute__((always_inline)) {
         const int kk = min(SPLITS * (it + 2) + sp, n_kt - 1), kv = min(SPLITS * (it + 1) + sp, n_kt - 1);
         const unsigned lk = KA(SPLITS * (it & 1) + sp), lv = VA(SPLITS * ((it + 1) & 1) + sp);
-        seq<0, KB * QB>([&](auto gc) __attribute__((always_inline)) {
-            constexpr int g = decltype(gc)::value, kb = g / QB, qb = g % QB;
-            constexpr int d0 = g * 2 * WL / (KB * QB), d1 = (g + 1) * 2 * WL / (KB * QB);
-            if constexpr (d0 < WL) gload_op(args.K, k_src, kk, lk, d0, d1 < WL ? d1 : WL);
-            if constexpr (d1 > WL) gload_op(args.V, v_src, kv, lv, d0 > WL ? d0 - WL : 0, d1 - WL);
-            if constexpr (decltype(act)::value) {
-                float p[4];
+        auto groups = [&](auto loads) __attribute__((always_inline)) {
+            seq<0, KB * QB>([&](auto gc) __attribute__((always_inline)) {
+                constexpr int g = decltype(gc)::value, kb = g / QB, qb = g % QB;
+                constexpr int d0 = g * 2 * WL / (KB * QB), d1 = (g + 1) * 2 * WL / (KB * QB);
+                if constexpr (decltype(loads)::value && d0 < WL)
+                    load_op(args.K, k_src, kk, lk, d0, d1 < WL ? d1 : WL, IntC<0>{});
+                if constexpr (decltype(loads)::value && d1 > WL)
+                    load_op(args.V, v_src, kv, lv, d0 > WL ? d0 - WL : 0, d1 - WL, IntC<0>{});
+                if constexpr (decltype(act)::value) {
+                    float p[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[qb][kb][r], SCALE_LOG2, -m[qb]));
-                l[qb] += (p[0] + p[1]) + (p[2] + p[3]);
-                u32x4 w = __builtin_bit_cast(u32x4, pf[kb / 2][qb]);
-                w[2 * (kb % 2)] = pack2(p[0], p[1]);
-                w[2 * (kb % 2) + 1] = pack2(p[2], p[3]);
-                pf[kb / 2][qb] = __builtin_bit_cast(bf16x8, w);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        });
+                    for (int r = 0; r < 4; ++r)
+                        p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[qb][kb][r], SCALE_LOG2, -m[qb]));
+                    l[qb] += (p[0] + p[1]) + (p[2] + p[3]);
+                    u32x4 w = __builtin_bit_cast(u32x4, pf[kb / 2][qb]);
+                    w[2 * (kb % 2)] = pack2(p[0], p[1]);
+                    w[2 * (kb % 2) + 1] = pack2(p[2], p[3]);
+                    pf[kb / 2][qb] = __builtin_bit_cast(bf16x8, w);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        if (partial(max(kk, kv))) {
+            if (partial(kk)) load_op(args.K, k_src, kk, lk, 0, WL, IntC<1>{});
+            else load_op(args.K, k_src, kk, lk, 0, WL, IntC<0>{});
+            if (partial(kv)) load_op(args.V, v_src, kv, lv, 0, WL, IntC<1>{});
+            else load_op(args.V, v_src, kv, lv, 0, WL, IntC<0>{});
+            groups(IntC<0>{});
+        } else {
+            groups(IntC<1>{});
+        }
     };
     auto slot_end = [&] {
         __builtin_amdgcn_sched_barrier(0);

@@ -773,8 +773,18 @@ rc_status describe(const rc_op_desc *d, const rc_schedule *s, rc_plan &p) {
             Kern k;
             // Two key splits of four waves each whose ring (16 bn Dh bytes)
             // leaves room for one workgroup per CU take turns on the matrix
-            // cores.
-            const bool turns = kv(d, s, "stages") == 4 && kv(d, s, "splits") == 2 && w == 4 && 16ll * bn * Dh > 81920;
+            // cores, where a workgroup has enough key tiles for the turns
+            // to pay for the slot more at either end: 16, 8 more with the
+            // causal mask and 8 more with a partial last tile (its loads
+            // are checked).  In step -> in turns, us, 16 heads of 128, 64 x
+            // 64 tiles: 12 tiles causal with 64 heads 25.8 -> 26.6; 13, the
+            // last partial, no mask 12.0 -> 12.9; 16 no mask 15.0 -> 14.0;
+            // 32 no mask 48.2 -> 43.8, causal 29.6 -> 27.7; 33, the last
+            // partial, causal 34.3 -> 33.2.  Not for chunks of 4 to 16 tiles
+            // (chunk 4, 16 tiles, no mask: 54.1 -> 58.1).
+            const bool turns = kv(d, s, "stages") == 4 && kv(d, s, "splits") == 2 && w == 4 &&
+                               16ll * bn * Dh > 81920 && chunk == 0 &&
+                               nkt >= 16 + (causal ? 8 : 0) + (S % bn ? 8 : 0);
             double scale_log2 = 1.4426950408889634 / std::sqrt((double)Dh);
             char sbuf[64];
             snprintf(sbuf, sizeof sbuf, "#define SCALE_LOG2 %.17gf\n", scale_log2);

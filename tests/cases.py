@@ -518,8 +518,8 @@ def ring_edge_jobs():
             for b in RING_EDGE_BLOCKS for n in RING_EDGE_TILES]
 
 
-# Attention whose two key splits take turns on the matrix cores (one
-# workgroup per CU: block_n x head dim of 8192): 1 to 5 key tiles, so that a
+# Attention whose two key splits fill a CU (one workgroup per CU: block_n x
+# head dim of 8192), too short to take turns: 1 to 5 key tiles, so that a
 # split has none, one or a few, with and without a partial last tile; one and
 # two query blocks a wave; every head dimension that admits it; work items of
 # 4 key tiles.
@@ -539,6 +539,27 @@ def pingpong_jobs():
                                f"splits=2,chunk={chunk}")
         if sched.validate() == "":          # a block twice the sequence is refused
             jobs.append((op, str(sched)))
+    return jobs
+
+
+# The same schedules at the fewest key tiles at which the turns are taken (16,
+# 8 more with the causal mask, 8 more with a partial last tile) and one more:
+# an even and an odd number of tiles, a last tile of one key and of all but
+# one, every head dimension, one and two query blocks a wave.  The first query
+# tiles of a causal sequence have one or two key tiles, so that a split has
+# none or one.
+TURNS_ATTN = [(d, bn, s, bm, causal)
+              for d, bn in ((128, 64), (64, 128), (256, 32)) for causal in (0, 1)
+              for least in (16 + 8 * causal,)
+              for s in (bn * least, bn * (least + 1), bn * (least + 7) + 1, bn * (least + 9) - 1)
+              for bm in (64, 128) if d < 256 or bm == 64]
+
+
+def turns_jobs():
+    jobs = []
+    for d, bn, s, bm, causal in TURNS_ATTN:
+        op = rc.Op(rc.RC_OP_ATTENTION, (1, 1, s, d), causal)
+        jobs.append((op, f"block_m={bm},block_n={bn},waves=4,mfma=16,stages=4,vec=8,unroll=1,order=1,occ=1,splits=2,chunk=0"))
     return jobs
 
 
@@ -633,7 +654,7 @@ def all_compile_jobs():
     op = rc.Op(rc.RC_OP_CONV2D, W.workload_op("conv3x3_n2_64x64_c320_k320").dims, rc.RC_FLAG_NO_ACT)
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
-    for op, text in ring_edge_jobs() + gemm_ring_jobs() + pingpong_jobs():
+    for op, text in ring_edge_jobs() + gemm_ring_jobs() + pingpong_jobs() + turns_jobs():
         jobs.append((op, [op.from_string(text)]))
     for dims, flags, text in TIGHT_ATTN:
         op = rc.Op(rc.RC_OP_ATTENTION, dims, flags)

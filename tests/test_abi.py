@@ -339,6 +339,19 @@ def test_kernel_defines():
         assert f(op.ref, ctypes.byref(sched.raw), i, buf, 8) == 1
 
 
+def test_splits_take_turns_only_with_key_tiles_enough():
+    # below the least number of tiles, or cut into chunks: in step
+    for op, text in cases.pingpong_jobs():
+        assert rc.kernel_defines(op, op.from_string(text))["PINGPONG"] == "0", (op.dims, text)
+    for s, causal, turns in ((1024, 0, 1), (960, 0, 0), (1500, 0, 1), (1471, 0, 0), (1536, 1, 1), (1472, 1, 0),
+                             (2047, 1, 1), (1980, 1, 0)):
+        op = rc.Op(rc.RC_OP_ATTENTION, (1, 1, s, 128), causal)
+        text = "block_m=64,block_n=64,waves=4,mfma=16,stages=4,vec=8,unroll=1,order=1,occ=1,splits=2,chunk=0"
+        assert rc.kernel_defines(op, op.from_string(text))["PINGPONG"] == str(turns), (s, causal)
+        sched = op.from_string(text.replace("chunk=0", "chunk=8"))
+        assert sched.validate() == "" and rc.kernel_defines(op, sched)["PINGPONG"] == "0"
+
+
 def test_launch_packs_the_same_argument_block():
     # Plan.launch passes its rc_args as packed bytes: the same bytes as the
     # structure, for every number of inputs, missing ones included.

@@ -7,6 +7,7 @@ sampled outputs.  Outputs are NaN-filled before each launch so an unwritten
 element fails.  Tolerances (see oracle.compare): 1e-4 for the fp32 GEMM,
 2e-2 for bf16 inputs with fp32 accumulation, relative to max(|ref|, RMS).
 """
+import math
 import os
 
 import numpy as np
@@ -110,6 +111,54 @@ def test_attention_splits_in_turns(job):
     host["K"] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(host["K"]) * ramp)
     y, _ = run(op, op.from_string(text), host)
     assert_parity(op, y, host, label=f"{op.dims} {text}")
+
+
+# Factors along the keys: rising ones (to 8 times the size) move the running
+# maximum again and again, by more than the lazy rescale's 2^8; flat and
+# falling ones leave the first tiles the weight that rising ones take away,
+# so that a wrong first slot or load shows.
+RAMPS = {"rising": (0.25, 8.0), "flat": (1.0, 1.0), "falling": (4.0, 0.25)}
+
+
+def check_attention(op, text, ramp):
+    """Against 64 bits, with the bound of the kernel's two roundings to bf16:
+    of the probabilities (2^-8 of each, so of sum p |v| / l) and of the
+    output.  The fp32 scores of 256 products that add up to a few hundred in
+    size are off by 1e-3 at most, a tenth of that in the exponent's units:
+    a tenth is added for them."""
+    host = W.host_inputs(op, seed=3)
+    f = np.linspace(*RAMPS[ramp], op.dims[2], dtype=np.float32)[None, None, :, None]
+    host["K"] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(host["K"]) * f)
+    y, _ = run(op, op.from_string(text), host)
+    S, D = op.dims[2:]
+    q, k, v = (gen.bf16_bits_to_f32(host[x]).astype(np.float64).reshape(-1, S, D) for x in "QKV")
+    worst = 0.0
+    for h, got in enumerate(y.reshape(-1, S, D)):
+        x = q[h] @ k[h].T / math.sqrt(D)
+        if op.flags & rc.RC_FLAG_CAUSAL:
+            x[np.triu_indices(S, 1)] = -np.inf
+        p = np.exp(x - x.max(axis=1, keepdims=True))
+        p /= p.sum(axis=1, keepdims=True)
+        o = p @ v[h]
+        bound = 1.1 * 2.0 ** -8 * (p @ np.abs(v[h]) + np.abs(o))
+        worst = max(worst, float(np.max(np.abs(got - o) / bound)))
+    print(f"[parity] {op.dims} {text} {ramp} worst share of the bound {worst:.3f}", flush=True)
+    assert worst <= 1.0
+
+
+@pytest.mark.parametrize("ramp", RAMPS)
+@pytest.mark.parametrize("job", range(len(cases.TURNS_ATTN)))
+def test_attention_splits_in_turns_at_their_least_tiles(job, ramp):
+    op, text = cases.turns_jobs()[job]
+    sched = op.from_string(text)
+    assert sched.validate() == "" and rc.kernel_defines(op, sched)["PINGPONG"] == "1"
+    check_attention(op, text, ramp)
+
+
+@pytest.mark.parametrize("ramp", ["flat", "falling"])
+@pytest.mark.parametrize("job", range(len(cases.pingpong_jobs())))
+def test_attention_two_splits_short_sequences(job, ramp):
+    check_attention(*cases.pingpong_jobs()[job], ramp)
 
 
 def test_gemm_sweep_has_18_legal_points():
