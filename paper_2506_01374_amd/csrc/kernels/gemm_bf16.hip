@@ -245,6 +245,7 @@ void rc_gemm_bf16(GemmBf16Args args) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform: scalar registers
+    __builtin_assume(wave >= 0 && wave < WM * WN);   // (known of tid: without it the offsets' divisions are signed ones)
     const int wm = wave / WN, wn = wave % WN;
 
     // ---- workgroup -> tile --------------------------------------------
@@ -930,6 +931,22 @@ void rc_gemm_bf16(GemmBf16Args args) {
 #else
     constexpr int STEADY_TILES = KTILES >= NSTAGE ? ((KTILES - (NSTAGE - 1)) & ~1) : 0;
 #endif
+    // The last tiles (at most NSTAGE, all of them when K has no more) are
+    // unrolled, so that their stages and waits are constants: rolled up, with
+    // a branch over the possible waits in each, they cost more than the
+    // pinned order saved up to about 1.5 rings of K.  With a second copy of
+    // the loop for partial tiles only where they are at least half of K and
+    // the tile is small: both copies unrolled spill larger ones.
+    // 1 x 1 filters, 512 rows, 640 channels out, 64 x 64 x 64 tiles (ring of
+    // 10), us a pass with the order left to the compiler / pinned, the last
+    // tiles rolled up / unrolled: 8 K tiles 4.85 / 5.36 / 4.33, 10 tiles 5.28
+    // / 6.37 / 4.63, 12 tiles 5.82 / 6.18 / 5.03, 16 tiles 6.93 / 7.03 /
+    // 5.72, 30 tiles 13.1 / 8.99 / 7.81.
+#ifdef RING_FREE
+    constexpr bool TAIL_CONST = false;
+#else
+    constexpr bool TAIL_CONST = !PART_TILES || (2 * STEADY_TILES <= KTILES && NB * FM * FN * ACCN <= 64);
+#endif
     run_tiles([&](auto part) __attribute__((always_inline)) {
 #if PART_TILES && !defined(RING_FREE)
         if constexpr (decltype(part)::value) {
@@ -945,6 +962,16 @@ void rc_gemm_bf16(GemmBf16Args args) {
         for (; t < STEADY_TILES; t += 2) {
             body7(t, IntC<0>{}, part, IntC<1>{});
             body7(t + 1, IntC<1>{}, part, IntC<1>{});
+        }
+        if constexpr (TAIL_CONST) {
+            // the stages of the tiles left, and with them every wait, constants
+            cur = STEADY_TILES % NSTAGE;
+            nx = (STEADY_TILES + 1) % NSTAGE;
+            fill = (STEADY_TILES + NSTAGE - 1) % NSTAGE;
+            seq<STEADY_TILES, KTILES>([&](auto tc) __attribute__((always_inline)) {
+                body7(decltype(tc)::value, IntC<decltype(tc)::value & 1>{}, part, IntC<0>{});
+            });
+            t = KTILES;
         }
 #ifndef RING_FREE
 #pragma nounroll
