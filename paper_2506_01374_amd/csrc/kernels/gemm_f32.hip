@@ -40,10 +40,13 @@
 #define RAGGED ((GM % TM) != 0 || (GN % TN) != 0 || (GK % TK) != 0)
 // Stages 2 runs as a ring of NST LDS buffers when the loads are 16-byte
 // vectors, a K tile is whole 16-row MFMA blocks, its 1 KiB wave-loads split
-// evenly over the waves and 32-bit buffer offsets reach both operands.
+// evenly over the waves and 32-bit buffer offsets reach both operands, K
+// rounded up to whole tiles (offsets past the end of K are formed too, and
+// their top bit marks them).
 #define WLOADS ((TM * TK + TN * TK) / 256)
+#define KUP (1ull * KTILES * TK)
 #define RING (STAGES == 2 && VEC == 4 && TK >= 16 && WLOADS % (WM * WN) == 0 &&                       \
-              4ull * GM * GK < 0x80000000ull && 4ull * GK * GN < 0x80000000ull)
+              4ull * GM * KUP < 0x80000000ull && 4ull * KUP * GN < 0x80000000ull)
 #define A_LOADS ((TM * TK) / (VEC * NT))
 #define B_LOADS ((TK * TN) / (VEC * NT))
 

@@ -352,6 +352,19 @@ def test_splits_take_turns_only_with_key_tiles_enough():
         assert sched.validate() == "" and rc.kernel_defines(op, sched)["PINGPONG"] == "0"
 
 
+@pytest.mark.parametrize("dims,bufs", [
+    # offsets of whole K tiles reach 2^31: the double buffer (33 and 65 floats a row)
+    ((16, 520000, 1004), 4), ((16, 530000, 1004), 0), ((530000, 16, 1004), 0)])
+def test_fp32_ring_buffers(dims, bufs):
+    op = rc.Op(rc.RC_OP_GEMM_F32, dims)
+    tm, tn = (16, 64) if dims[0] == 16 else (64, 16) if dims[1] == 16 else (64, 64)
+    wm, wn = (1, 2) if tm == 16 else (2, 1) if tn == 16 else (2, 2)
+    sched = op.from_string(f"tile_m={tm},tile_n={tn},tile_k=32,waves_m={wm},waves_n={wn},vec=4,stages=2,unroll=1,layout=0")
+    assert sched.validate() == ""
+    lds = rc.describe(op, sched)[0]["lds_bytes"]
+    assert lds == (4 * bufs * (tm + tn) * 32 if bufs else 8 * (tm * 33 + 32 * (tn + 1)))
+
+
 def test_launch_packs_the_same_argument_block():
     # Plan.launch passes its rc_args as packed bytes: the same bytes as the
     # structure, for every number of inputs, missing ones included.
