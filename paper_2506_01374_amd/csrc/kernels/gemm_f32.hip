@@ -223,7 +223,20 @@ extern "C" __global__ __launch_bounds__(256) void rc_gemm_f32_splitk_reduce(Gemm
 // 34.9 us double-buffered, 29.7 us with the ring and each tile's loads, reads
 // and MFMAs in turn, 27.6 us (89 TFLOP/s) interleaved; the 688 tiles are 2.7 a
 // CU, and the three of the fuller ones take 18.6 us of matrix time.
-#define NST 4
+//
+// NST, the depth, is 4, and 3 where that lets the whole grid be resident and
+// 4 does not (2048 x 1024 x 128 in 64 x 32 x 32 tiles, 4 workgroups a CU: 8.1
+// us double-buffered, 8.3 with 48 KiB, 7.1 with 36), and there are never more
+// buffers than K tiles (1600 x 1760 x 64 in 16 x 32 x 32 tiles, us: 7.5
+// double-buffered, 8.0 with four buffers, 7.1 with two).
+// The last tiles are unrolled, so that their waits and buffers are constants
+// (2048 x 1024 x 96 in 64 x 32 x 32 tiles: 6.7 -> 6.2 us).
+#define STAGE_BYTES (4 * (TM + TN) * TK)
+#define N_TILES (1ull * ((GM + TM - 1) / TM) * ((GN + TN - 1) / TN))
+#define RESIDENT(bytes) (N_TILES <= 256 * (163840 / (bytes)))
+#define BUFS(n) ((n) < KTILES ? (n) : KTILES)
+#define NST (!RESIDENT(BUFS(4) * STAGE_BYTES) && RESIDENT(BUFS(3) * STAGE_BYTES) ? 3 : 4)
+#define NBUF BUFS(NST)
 #define NW (WM * WN)
 #define LPW (WLOADS / NW)                        // wave-loads per wave and K tile
 #define A_WL (TM * TK / 256)                     // wave-loads of the A tile (the rest are B's)
@@ -249,9 +262,10 @@ __device__ __forceinline__ int brow(int k) { return (k & ~15) + 4 * (k & 3) + ((
 __device__ __forceinline__ int nswz(int p) { return TN == 64 ? 4 * (p & 3) : TN == 32 ? 4 * ((p >> 1) & 1) : 0; }
 
 extern "C" __global__ __launch_bounds__(NT) void rc_gemm_f32(GemmF32Args args) {
-    __shared__ __attribute__((aligned(16))) float ring[NST * STAGE_FLOATS];
+    __shared__ __attribute__((aligned(16))) float ring[NBUF * STAGE_FLOATS];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __builtin_assume(wave >= 0 && wave < NW);
     const int wm = wave / WN, wn = wave % WN;
     const int q = lane >> 4, c = lane & 15;
     // Workgroups reach the 8 XCDs round-robin: each XCD takes a contiguous
@@ -373,7 +387,7 @@ extern "C" __global__ __launch_bounds__(NT) void rc_gemm_f32(GemmF32Args args) {
 #pragma unroll
     for (int u = 0; u < NST - 1; ++u)
         if (u < KTILES) issue(u, u);
-    if (KTILES > 2) {
+    if (KTILES > 2 && NST > 3) {
         WAIT_VM(2 * LPW);
     } else if (KTILES > 1) {
         WAIT_VM(LPW);
@@ -386,16 +400,16 @@ extern "C" __global__ __launch_bounds__(NT) void rc_gemm_f32(GemmF32Args args) {
     int cur = 0;
     auto tile = [&](int t, auto par, auto steady) __attribute__((always_inline)) {
         constexpr int P = decltype(par)::value;
-        const int nx = (cur + 1) % NST, st = (cur + NST - 1) % NST;
+        const int nx = (cur + 1) % NBUF, st = (cur + NST - 1) % NBUF;
         // Tile t + 1 has landed (of the steady part's tiles t + 2 is in
-        // flight), and every wave is done with tile t - 1, whose buffer tile
+        // flight in a ring of four), and every wave is done with tile t - 1, whose buffer tile
         // t + NST - 1 takes: its reads were consumed by MFMAs issued before.
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (decltype(steady)::value) {
-            WAIT_VM(LPW);
+            WAIT_VM((NST - 3) * LPW);
             asm volatile("s_barrier" ::: "memory");
         } else if (t + 1 < KTILES) {
-            if (t + 2 < KTILES) {
+            if (NST > 3 && t + 2 < KTILES) {
                 WAIT_VM(LPW);
             } else {
                 WAIT_VM(0);
@@ -417,11 +431,10 @@ extern "C" __global__ __launch_bounds__(NT) void rc_gemm_f32(GemmF32Args args) {
         tile(t, IntC<0>{}, IntC<1>{});
         tile(t + 1, IntC<1>{}, IntC<1>{});
     }
-#pragma nounroll
-    for (; t < KTILES; t += 2) {
-        tile(t, IntC<0>{}, IntC<0>{});
-        if (t + 1 < KTILES) tile(t + 1, IntC<1>{}, IntC<0>{});
-    }
+    cur = STEADY_TILES % NBUF;
+    seq<STEADY_TILES, KTILES>([&](auto u) __attribute__((always_inline)) {
+        tile(decltype(u)::value, IntC<decltype(u)::value & 1>{}, IntC<0>{});
+    });
 #undef WAIT_VM
 
 #pragma unroll

@@ -599,6 +599,18 @@ def gemm_ring_jobs():
     return jobs
 
 
+# The fp32 ring at a depth of three (its grid is resident on the chip with
+# three buffers a workgroup and not with four): K around the depth, both
+# layouts of B, more rows than columns and fewer (the order of the tiles).
+GEMM_RING3_DIMS = [(m, n, k) for m, n in ((1469, 1532), (1532, 1468)) for k in (124, 128, 132, 160, 196, 260)]
+
+
+def gemm_ring3_jobs():
+    return [(rc.Op(rc.RC_OP_GEMM_F32, dims),
+             f"tile_m=64,tile_n=64,tile_k=32,waves_m=2,waves_n=2,vec=4,stages=2,unroll=1,layout={lay}")
+            for dims in GEMM_RING3_DIMS for lay in (0, 1)]
+
+
 # Schedules the search can emit: random legal transformation sequences of
 # length 12 from P0 (the rollouts of Sec. 3.2), seeded, at the small shapes.
 WALK_KEYS = ("gemm", "attn_causal", "mlp", "moe", "conv")
@@ -654,7 +666,7 @@ def all_compile_jobs():
     op = rc.Op(rc.RC_OP_CONV2D, W.workload_op("conv3x3_n2_64x64_c320_k320").dims, rc.RC_FLAG_NO_ACT)
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
-    for op, text in ring_edge_jobs() + gemm_ring_jobs() + pingpong_jobs() + turns_jobs():
+    for op, text in ring_edge_jobs() + gemm_ring_jobs() + gemm_ring3_jobs() + pingpong_jobs() + turns_jobs():
         jobs.append((op, [op.from_string(text)]))
     for dims, flags, text in TIGHT_ATTN:
         op = rc.Op(rc.RC_OP_ATTENTION, dims, flags)

@@ -353,6 +353,10 @@ def test_splits_take_turns_only_with_key_tiles_enough():
 
 
 @pytest.mark.parametrize("dims,bufs", [
+    # never more buffers than K tiles of 32; four at most
+    ((83, 92, 20), 1), ((83, 92, 64), 2), ((83, 92, 96), 3), ((83, 92, 100), 4), ((83, 92, 1000), 4),
+    # three where only they let 3 workgroups a CU be resident
+    ((1472, 1536, 128), 3), ((1408, 1472, 128), 4), ((2048, 1600, 128), 4), ((1472, 1536, 64), 2),
     # offsets of whole K tiles reach 2^31: the double buffer (33 and 65 floats a row)
     ((16, 520000, 1004), 4), ((16, 530000, 1004), 0), ((530000, 16, 1004), 0)])
 def test_fp32_ring_buffers(dims, bufs):

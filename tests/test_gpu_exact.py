@@ -244,6 +244,17 @@ def test_fp32_ring_edges_integer_inputs_bitwise(job):
     assert np.array_equal(W.output_to_f64(op, out), host["A"].astype(np.float64) @ host["B"].astype(np.float64))
 
 
+@pytest.mark.parametrize("job", range(2 * len(cases.GEMM_RING3_DIMS)))
+def test_fp32_ring_of_three_integer_inputs_bitwise(job):
+    op, text = cases.gemm_ring3_jobs()[job]
+    M, N, K = op.dims
+    sched = op.from_string(text)
+    assert rc.describe(op, sched)[0]["lds_bytes"] == 3 * 128 * 32 * 4
+    host = {"A": gen.int_valued_f32(19, 1, (M, K), 4), "B": gen.int_valued_f32(19, 2, (K, N), 4)}
+    _, _, out, _ = launch(op, sched, host)
+    assert np.array_equal(W.output_to_f64(op, out), host["A"].astype(np.float64) @ host["B"].astype(np.float64))
+
+
 @pytest.mark.parametrize("sched_text", ["tuned", "default", cases.CONV_FULL_ALT])
 def test_conv_full_size_ones_padding_counts(sched_text):
     # Ones input, ones filters, zero bias, no activation: interior outputs
