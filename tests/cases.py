@@ -518,6 +518,33 @@ def ring_edge_jobs():
             for b in RING_EDGE_BLOCKS for n in RING_EDGE_TILES]
 
 
+# The same around a depth of three, whose loads are issued from the start of a
+# tile: K of 1 to 7 tiles.
+RING3_BLOCKS = [(256, 128, 64, 2, 4, 16, 7, 8, 1, 1, 1, 1), (128, 64, 64, 2, 2, 16, 7, 8, 1, 1, 0, 2),
+                (128, 64, 64, 2, 2, 32, 7, 8, 1, 1, 2, 2)]
+
+
+def ring3_edge_jobs():
+    return [(rc.Op(rc.RC_OP_CONV2D, (1, 18, 15, b[2] * n, 128, 1, 1, 0), rc.RC_FLAG_NO_ACT), _block("", *b) + ",fuse=1")
+            for b in RING3_BLOCKS for n in range(1, 8)]
+
+
+# Ring variants that spill in the pinned order and are built with the order
+# left to the compiler (RING_FREE): 1 x 1 filters of a few depths, padded
+# 3 x 3 filters, and gate and up projections of experts with partial tiles.
+_FREE_BLOCK = (64, 320, 32, 4, 1, 16, 7, 8, 1, 1, 0, 2)
+RING_FREE_CONV = [(dims, _block("", *_FREE_BLOCK) + ",fuse=1")
+                  for dims in ((1, 18, 17, 384, 320, 1, 1, 0), (1, 16, 16, 416, 320, 1, 1, 0), (2, 9, 11, 64, 320, 3, 3, 1))]
+RING_FREE_MOE = [(dims, _block("up.", 128, 128, 32, 2, 2, 16, 7, 8, 1, 1, 2, 2) + ","
+                  + _block("down.", 128, 128, 32, 2, 2, 16, 7, 8, 1, 1, 2, 1) + ",fuse=1,up.skip=1,down.skip=1")
+                 for dims in ((500, 256, 4, 256, 2), (333, 512, 4, 512, 1))]
+
+
+def ring_free_jobs():
+    return ([(rc.Op(rc.RC_OP_CONV2D, d, rc.RC_FLAG_NO_ACT), t) for d, t in RING_FREE_CONV]
+            + [(rc.Op(rc.RC_OP_MOE, d), t) for d, t in RING_FREE_MOE])
+
+
 # Attention whose two key splits fill a CU (one workgroup per CU: block_n x
 # head dim of 8192), too short to take turns: 1 to 5 key tiles, so that a
 # split has none, one or a few, with and without a partial last tile; one and
@@ -561,6 +588,18 @@ def turns_jobs():
         op = rc.Op(rc.RC_OP_ATTENTION, (1, 1, s, d), causal)
         jobs.append((op, f"block_m={bm},block_n={bn},waves=4,mfma=16,stages=4,vec=8,unroll=1,order=1,occ=1,splits=2,chunk=0"))
     return jobs
+
+
+# Attention for scores far from zero: in turns, in step with two splits and
+# one, and the variants that reduce the maximum of every tile.
+EDGE_ATTN = [((1, 1, 1024, 128), 0, 64, 64, 2), ((1, 1, 1536, 128), 1, 64, 64, 2), ((1, 1, 320, 128), 0, 64, 64, 2),
+             ((1, 1, 320, 128), 1, 64, 32, 1), ((1, 2, 256, 256), 1, 32, 32, 1), ((1, 1, 333, 64), 0, 64, 32, 1)]
+
+
+def edge_attn_jobs():
+    return [(rc.Op(rc.RC_OP_ATTENTION, dims, causal),
+             f"block_m={bm},block_n={bn},waves={4 if bm == 64 else 1},mfma=16,stages=4,vec=8,unroll=1,order=1,occ=1,"
+             f"splits={splits},chunk=0") for dims, causal, bm, bn, splits in EDGE_ATTN]
 
 
 # Attention variants at the limit of their registers (a register more in the
@@ -666,7 +705,8 @@ def all_compile_jobs():
     op = rc.Op(rc.RC_OP_CONV2D, W.workload_op("conv3x3_n2_64x64_c320_k320").dims, rc.RC_FLAG_NO_ACT)
     jobs.append((op, [op.from_string(TUNED["conv3x3_n2_64x64_c320_k320"]), op.default(),
                       op.from_string(CONV_FULL_ALT)]))
-    for op, text in ring_edge_jobs() + gemm_ring_jobs() + gemm_ring3_jobs() + pingpong_jobs() + turns_jobs():
+    for op, text in (ring_edge_jobs() + ring3_edge_jobs() + ring_free_jobs() + gemm_ring_jobs() + gemm_ring3_jobs()
+                     + pingpong_jobs() + turns_jobs() + edge_attn_jobs()):
         jobs.append((op, [op.from_string(text)]))
     for dims, flags, text in TIGHT_ATTN:
         op = rc.Op(rc.RC_OP_ATTENTION, dims, flags)

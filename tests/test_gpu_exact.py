@@ -232,6 +232,31 @@ def test_ring_gemm_depth_edges_integer_inputs_bitwise(job):
                           oracle.bf16_to_f64(oracle.bf16_from_f64(exact)).reshape(-1, K))
 
 
+@pytest.mark.parametrize("job", range(7 * len(cases.RING3_BLOCKS)))
+def test_ring_gemm_depth_three_integer_inputs_bitwise(job):
+    # At most 7 x 64 products of integers up to 8: exact, as above.
+    op, text = cases.ring3_edge_jobs()[job]
+    sched = op.from_string(text)
+    assert rc.kernel_defines(op, sched)["NSTAGE"] == "3"
+    _check_integer_conv(op, sched)
+
+
+@pytest.mark.parametrize("job", range(len(cases.RING_FREE_CONV)))
+def test_ring_gemm_free_order_integer_inputs_bitwise(job):
+    # At most 576 products of integers up to 8: exact, as above.
+    op, text = cases.ring_free_jobs()[job]
+    sched = op.from_string(text)
+    assert rc.kernel_defines(op, sched)["RING_FREE"] == "1"
+    _check_integer_conv(op, sched)
+
+
+def _check_integer_conv(op, sched):
+    host = _int_conv_inputs(*op.dims[:7], seed=17)
+    ref = oracle.bf16_to_f64(oracle.conv2d_bf16(host["x"], host["w"], host["bias"], pad=op.dims[7], act=False))
+    _, _, out, _ = launch(op, sched, host)
+    assert np.array_equal(W.output_to_f64(op, out).reshape(ref.shape), ref)
+
+
 @pytest.mark.parametrize("job", range(len(cases.GEMM_RING_TILES) * len(cases.GEMM_RING_K)))
 def test_fp32_ring_edges_integer_inputs_bitwise(job):
     # Integers in [-4, 4]: every partial sum is exact in fp32 in any order.

@@ -113,6 +113,56 @@ def test_attention_splits_in_turns(job):
     assert_parity(op, y, host, label=f"{op.dims} {text}")
 
 
+@pytest.mark.parametrize("job", range(len(cases.RING_FREE_MOE)))
+def test_moe_ring_free_order_partial_tiles(job):
+    op, text = cases.ring_free_jobs()[len(cases.RING_FREE_CONV) + job]
+    sched = op.from_string(text)
+    built = [rc.kernel_defines(op, sched, i) for i in range(len(rc.describe(op, sched)))]
+    assert any("RING_FREE" in d and "ROWSKIP" in d for d in built)
+    host = W.host_inputs(op, seed=5)
+    y, _ = run(op, sched, host)
+    assert_parity(op, y, host, label=f"{op.dims} {text}")
+
+
+# Scores far from zero: the running maximum moves by more than the exponent's
+# range, starts far below it, or half of the scores overflow to minus
+# infinity.  One split and two, in step and in
+# turns, and the variants that reduce the maximum of every tile.
+@pytest.mark.parametrize("what", ["huge", "low", "inf"])
+@pytest.mark.parametrize("job", range(len(cases.EDGE_ATTN)))
+def test_attention_scores_far_from_zero(job, what):
+    op, text = cases.edge_attn_jobs()[job]
+    S, D = op.dims[2:]
+    sched = op.from_string(text)
+    assert sched.validate() == ""
+    host = W.host_inputs(op, seed=7)
+    # one direction: every score is q0 k0 / sqrt(D), with one key largest by
+    # far for each query (key i for query i where the mask hides the rest)
+    shape = host["Q"].shape
+    q, k = np.zeros(shape, np.float32), np.zeros(shape, np.float32)
+    step = np.arange(S, dtype=np.float32)
+    if what == "huge":            # up to 2^26: neighbours are 2^14 and more apart
+        q[..., 0], k[..., 0] = 2.0 ** 10, np.exp2(np.floor(step * (12.0 / S))) * 16
+    elif what == "low":           # from -2^24, the second half of the keys at 0
+        q[..., 0], k[..., 0] = 2.0 ** 12, -(2.0 ** 12) * (step < S // 2)
+    else:                         # half of the keys at minus infinity (never all of a query's)
+        q[..., 0], k[..., 0] = 1.0e20, np.where(step % 2 == 1, -1.0e20, 0.0)
+    host["Q"], host["K"] = gen.f32_to_bf16_bits(q), gen.f32_to_bf16_bits(k)
+    y, _ = run(op, sched, host)
+    qd, kd, v = (gen.bf16_bits_to_f32(host[x]).astype(np.float64).reshape(-1, S, D) for x in "QKV")
+    for h, got in enumerate(y.reshape(-1, S, D)):
+        x = qd[h][:, :1] * kd[h][:, 0][None, :] / math.sqrt(D)
+        if op.flags & rc.RC_FLAG_CAUSAL:
+            x[np.triu_indices(S, 1)] = -np.inf
+        p = np.exp(x - x.max(axis=1, keepdims=True))
+        p /= p.sum(axis=1, keepdims=True)
+        o = p @ v[h]
+        # the two roundings to bf16; the scores are exact, and the rounding
+        # of the maximum is common to all that count
+        bound = 1.1 * 2.0 ** -8 * (p @ np.abs(v[h]) + np.abs(o))
+        assert np.all(np.abs(got - o) <= bound), (what, float(np.max(np.abs(got - o) / bound)))
+
+
 # Factors along the keys: rising ones (to 8 times the size) move the running
 # maximum again and again, by more than the lazy rescale's 2^8; flat and
 # falling ones leave the first tiles the weight that rising ones take away,
