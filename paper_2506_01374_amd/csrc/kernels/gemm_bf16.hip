@@ -692,17 +692,13 @@ void rc_gemm_bf16(GemmBf16Args args) {
         b_off7[j] = (unsigned)(((size_t)(n0 + row) * GK + lc * 8) * 2);
     }
     // `koff` is wave-uniform and added to the lane's byte offset; the range
-    // check covers the sum, so an offset of OOB stays out of range
-    // (the readfirstlanes are free for values already in scalar registers;
-    // they make sure of it for the few variants where the compiler moves
-    // wave-uniform values to vector registers, which the asm cannot take)
+    // check covers the sum, so an offset of OOB stays out of range.  The
+    // resource, koff and the LDS address have to be in scalar registers: the
+    // resource is read through readfirstlane, the other two follow from the
+    // wave index, which is.
     auto dma = [&](unsigned off, const i32x4 &rs, unsigned koff, unsigned lds_addr) {
-        i32x4 rsu;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) rsu[r] = rs[r];
         asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                     :: "v"(off), "s"(rsu), "s"(koff),
-                        "s"(lds_addr) : "memory", "m0");
+                     :: "v"(off), "s"(rs), "s"(koff), "s"(lds_addr) : "memory", "m0");
     };
     const unsigned ring0 = (unsigned)(size_t)(lds_p)ring;
     // wave-load d (0 .. LPT - 1: the A tile's, then each weight tile's) of K
