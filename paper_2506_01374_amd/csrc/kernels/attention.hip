@@ -22,7 +22,8 @@
 //                per key split and the scores of the split's next tile
 //                computed ahead of this tile's softmax (ComputeLocation)
 //   VEC          bf16 per global load of K (Vectorize)
-//   UNROLL       unroll factor of the key-tile loop (Unroll)
+//   UNROLL       unroll factor of the key-tile loop (Unroll; no effect where
+//                the splits take turns)
 //   ORDER        0: query tiles in order; 1: longest (last) query tiles
 //                first; 2: paired - workgroup b and b + half take query
 //                tiles t and NQT-1-t, so that co-resident pairs carry equal
@@ -843,7 +844,7 @@ void rc_attention(AttnArgs args) {
     // issues the same number; nothing reads them.
     // 1 x 24 x 4096 x 128, 128 x 64 tiles: 203.5 us in step, 197.7 with the
     // reduction of the row maximum left to the tiles that move it (rescale),
-    // 182 in turns (1.13 PFLOP/s; a slower card 212 -> 192).  One workgroup a
+    // 182 in turns (1.13 PFLOP/s; a slower card 209 -> 191).  One workgroup a
     // CU only: two of 64 KiB already fill each other's gaps (causal 1 x 32 x
     // 1024 x 128: 17.6 us in step, 18.0 in turns; causal 2 x 16 x 777 x 64:
     // 9.1 and 10.6), and only with key tiles enough (the host's rule).

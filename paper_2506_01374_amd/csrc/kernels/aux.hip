@@ -132,8 +132,8 @@ extern "C" __global__ __launch_bounds__(256) void rc_splitk_swiglu_bf16(EwArgs a
 //     writes the counts to counts[b][*].  With one block (a decode step: up
 //     to 1,024 routed rows) it is not launched: rc_moe_prep sums its waves'
 //     counts, which it needs anyway, and a launch costs more than the sums
-//     (32 tokens of 64 experts 2048 x 1408, top-6: 195.3 us with the launch,
-//     193.7 without; 6 tokens of 8 experts 512 x 384, top-1: 16.6 and 13.9).
+//     (6 tokens of 8 experts 512 x 384, top-1: 12.2 us with the launch, 11.0
+//     without; 32 tokens of 64 experts 2048 x 1408, top-6: 190.5 and 189.0).
 //   rc_moe_prep: block b reads the whole counts table; thread e sums
 //     column e (all blocks: the expert's total; blocks before b: the rows
 //     of expert e that precede this block).  A block-wide exclusive scan of

@@ -771,10 +771,11 @@ void rc_gemm_bf16(GemmBf16Args args) {
     // next.  The scheduling barriers keep the order written here; the
     // scheduler would otherwise gather the reads at the end of the k-step.
     // (All loads first, then reads and MFMAs in the scheduler's order -> this
-    // order: 3 x 3 convolution 2 x 64 x 64 x 320 -> 320 in 64 x 160 x 64 tiles
-    // 25.4 -> 21.2 us; 1000 x 4096 x 4096 in 128 x 128 x 64 tiles 38.7 -> 33.7
-    // us; gated MLP 2048 x 4096 x 14336 639 -> 616 us, near the power limit;
-    // MoE 4096 tokens 551 -> 524 us; weight streams of 16 rows unchanged.)
+    // order, the last tiles unrolled: 3 x 3 convolution 2 x 64 x 64 x 320 ->
+    // 320 in 64 x 160 x 64 tiles 25.4 -> 21.0 us; 1000 x 4096 x 4096 in 128 x
+    // 128 x 64 tiles 39.9 -> 34.1 us; gated MLP 2048 x 4096 x 14336 651 -> 621
+    // us, near the power limit; MoE 4096 tokens 558 -> 531 us; weight streams
+    // of 16 and 32 rows 1 % less.)
 #ifdef RING_FREE
     // The order left to the compiler, for the few register-bound variants
     // that spill in the order above: a tile's loads first, then each

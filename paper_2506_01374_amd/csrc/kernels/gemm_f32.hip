@@ -221,8 +221,9 @@ extern "C" __global__ __launch_bounds__(256) void rc_gemm_f32_splitk_reduce(Gemm
 // among each other in a pinned order (UNROLL has no effect here: the loop is
 // always unrolled by two tiles).  1000 x 1364 x 900 in 64 x 32 x 32 tiles:
 // 34.9 us double-buffered, 29.7 us with the ring and each tile's loads, reads
-// and MFMAs in turn, 27.6 us (89 TFLOP/s) interleaved; the 688 tiles are 2.7 a
-// CU, and the three of the fuller ones take 18.6 us of matrix time.
+// and MFMAs in turn, 27.6 us interleaved, 27.0 us (91 TFLOP/s) with the
+// XCDs' ranges along the rows; the 688 tiles are 2.7 a CU, and the three of the
+// fuller ones take 18.6 us of matrix time.
 //
 // NST, the depth, is 4, and 3 where that lets the whole grid be resident and
 // 4 does not (2048 x 1024 x 128 in 64 x 32 x 32 tiles, 4 workgroups a CU: 8.1

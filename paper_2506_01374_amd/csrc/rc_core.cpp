@@ -412,6 +412,7 @@ std::string check_schedule(const rc_op_desc *d, const rc_schedule *s) {
             if (lay == 0 && tn % vec) return fmt("vec %d does not divide tile_n %d", vec, tn);
             const int64_t ktiles = (K + tk - 1) / tk;
             if (ktiles % un) return fmt("unroll %d does not divide the %lld K tiles", un, (long long)ktiles);
+            // (stages 2 as a ring: up to four buffers, 64 KiB at most)
             int64_t lds = (int64_t)st * (tm * (tk + 1) + tk * (tn + 1)) * 4;
             if (lds > LDS_LIMIT) return fmt("LDS %lld B exceeds limit", (long long)lds);
             return "";
