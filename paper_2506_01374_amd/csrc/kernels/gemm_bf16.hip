@@ -798,12 +798,22 @@ void rc_gemm_bf16(GemmBf16Args args) {
         const int r = (m * NRD * 4 + 3 * NMF - 1) / (3 * NMF);
         return r < NRD ? r : NRD;
     };
-    // Loads issued before MFMA s of a tile: spread over the whole tile, or,
-    // in a ring of three, where a load has to land within one tile, one per
-    // MFMA from the start (736-token MLP 3072 x 6912 in 128 x 128 x 64 tiles:
-    // 197.0 us spread, 190.8 so, 193.3 all before the first MFMA).
+    // Loads issued before MFMA s of a tile: spread over the whole tile; one
+    // per MFMA from the start in a ring of three, where a load has to land
+    // within one tile (736-token MLP 3072 x 6912 in 128 x 128 x 64 tiles:
+    // 197.0 us spread, 190.8 so, 193.3 all before the first MFMA); and all
+    // before the first MFMA where that still comes too late: a short ring
+    // (three or four) whose CU other workgroups share, or a ring of three
+    // with fewer than three MFMAs to a load (1000 x 2048 -> 2048 in 32 x 64 x
+    // 64 tiles of one wave, us with the order left to the compiler / spread /
+    // so: 19.5 / 22.9 / 19.4; 3 x 3 convolution 2 x 64 x 64 x 320 -> 320 in
+    // 128 x 64 x 32 tiles of two waves: 43.5 / 46.6 / 41.3).  Not for more
+    // than 128 accumulators, whose variants keep the registers they have.
+    constexpr bool SHARED_CU = 2 * NSTAGE * STAGE_ELEMS * 2 <= 163840;
+    constexpr bool LOADS_FIRST = ((NSTAGE <= 4 && SHARED_CU) || (NSTAGE == 3 && KS * NMF < 3 * LPT)) &&
+                                 NB * FM * FN * ACCN <= 128;
     constexpr auto loads_before = [](int s) constexpr {
-        const int d = NSTAGE > 3 || LPT > KS * NMF ? s * LPT / (KS * NMF) : s;
+        const int d = LOADS_FIRST ? (s > 0 ? LPT : 0) : NSTAGE > 3 || LPT > KS * NMF ? s * LPT / (KS * NMF) : s;
         return d < LPT ? d : LPT;
     };
     auto kstep = [&](const Frags &cur, const bf16_t *ln, int ksn, Frags &nxt, auto ksc, auto loads, int kt, unsigned sb,
