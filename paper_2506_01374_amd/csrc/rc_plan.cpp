@@ -112,8 +112,17 @@ const std::vector<std::string> &compile_options() {
 
 std::string full_source(const Source &s) { return s.defines + "\n" + s.file; }
 
-std::string cache_key(const Source &s) {
-    std::string k = full_source(s);
+// Hash of what every variant of a kernel source shares: its text, the
+// compile options and the compiler.  Formed once per source (the texts are
+// the library's own literals): hashing some 60 KB again for each kernel of
+// each plan was most of creating a plan whose code objects are cached.
+uint64_t source_hash(const char *file) {
+    static std::mutex mu;
+    static std::map<const char *, uint64_t> known;
+    std::lock_guard<std::mutex> g(mu);
+    auto it = known.find(file);
+    if (it != known.end()) return it->second;
+    std::string k = file;
     for (auto &o : compile_options()) k += "\x1f" + o;
     int maj = 0, min = 0;
     hiprtcVersion(&maj, &min);
@@ -121,8 +130,12 @@ std::string cache_key(const Source &s) {
     // the compiler behind hipRTC is identified by the library actually loaded
     Dl_info info;
     if (dladdr((void *)&hiprtcCompileProgram, &info) && info.dli_fname) k += "\x1f" + std::string(info.dli_fname);
+    return known[file] = fnv1a(k + "\x1f");
+}
+
+std::string cache_key(const Source &s) {
     char hex[32];
-    snprintf(hex, sizeof hex, "%016llx", (unsigned long long)fnv1a(k));
+    snprintf(hex, sizeof hex, "%016llx", (unsigned long long)fnv1a(s.defines, source_hash(s.file)));
     return std::string(s.entry) + "_" + hex;
 }
 

@@ -327,6 +327,21 @@ def test_spilled_attention_is_compiled_once(tmp_path):
     assert _objects(tmp_path, op, text, "rc_attention") == (rc.RC_ERR_ILLEGAL_SCHEDULE, 1)
 
 
+def test_code_objects_are_named_by_source_and_definitions(tmp_path):
+    # one object per entry and set of definitions, found again by a later call
+    op = rc.Op(rc.RC_OP_GEMM_F32, (83, 92, 64))
+    texts = [f"tile_m=16,tile_n={tn},tile_k=32,waves_m=1,waves_n=1,vec=4,stages={st},unroll=1,layout=0"
+             for tn in (16, 32) for st in (1, 2)]
+    for _ in range(2):
+        for n, text in enumerate(texts):
+            assert _objects(tmp_path, op, text, "rc_gemm_f32")[0] == rc.RC_OK
+    assert len(os.listdir(tmp_path)) == len(texts)
+    stamp = {f: os.stat(tmp_path / f).st_mtime_ns for f in os.listdir(tmp_path)}
+    big = rc.Op(rc.RC_OP_GEMM_F32, (83, 92, 96))          # the same schedule, other sizes
+    assert _objects(tmp_path, big, texts[0], "rc_gemm_f32") == (rc.RC_OK, len(texts) + 1)
+    assert all(os.stat(tmp_path / f).st_mtime_ns == t for f, t in stamp.items())
+
+
 def test_kernel_defines():
     op = rc.Op(rc.RC_OP_ATTENTION, (1, 24, 4096, 128))
     sched = op.from_string(cases.TUNED["attention_noncausal_b1_h24_s4096_d128"])
